@@ -296,7 +296,7 @@ h2_status h2_matvec(h2_handle A, const double *x, double *y, void *stream);
 h2_status h2_matvec_noalloc(h2_handle A, const double *x, double *y, void *stream);
 
 /* Schedule of the single-vector products (h2_matvec, h2_matvec_noalloc, and
- * h2_matmat on FP64 handles) of a handle with full storage.
+ * the single-vector products of h2_matmat) of a handle with full storage.
  *  H2_SCHEDULE_MERGED (default): after the upsweep, one launch multiplies the
  *    coupling blocks of every level and the dense near-field blocks.
  *  H2_SCHEDULE_STREAMED: the near field y_near = D x, which does not need
@@ -330,10 +330,14 @@ h2_status h2_set_schedule(h2_handle A, int schedule, int near_wg_per_cu, double 
  * dense contraction.
  *  X  device, column-major n x nrhs, leading dimension ldx >= n, tree order.
  *  Y  device, column-major n x nrhs, leading dimension ldy >= n.
- * H2_FP64 handles, and handles stored by halves, run nrhs single-vector
- * products; other H2_FP32 and H2_BF16_SCALED handles
- * run on the matrix cores (FP32 MFMA), 32 right-hand sides per pass.  The first
- * such call on a handle times the candidate launch shapes (the block loop's
+ * Handles stored by halves, and calls with one right-hand side on H2_FP64
+ * handles, run nrhs single-vector products; the others run on the matrix cores,
+ * 32 right-hand sides per pass (FP64 MFMA and FP64 sums for H2_FP64, FP32 MFMA
+ * for H2_FP32 and H2_BF16_SCALED).  The first such call on a handle allocates
+ * the tiles (two per tree node and two per leaf); on an H2_FP64 handle a call
+ * that finds no memory for them, or comes first while its stream is being
+ * captured, runs single-vector products instead.  The first call on an H2_FP32
+ * or H2_BF16_SCALED handle also times the candidate launch shapes (the block loop's
  * prefetch depth 0..7 as listed at h2_batch_tuning, one workgroup per item
  * group or a persistent grid of 1 or 2 workgroups per compute unit, and the
  * MFMA tile width 16 or 32 for passes of at most 16 right-hand sides) on its

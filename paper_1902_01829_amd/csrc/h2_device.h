@@ -198,6 +198,26 @@ struct MmConfig {
 };
 hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg, hipStream_t st);
 
+// ---- many right-hand sides, FP64 matrices (h2_mm64.hip)
+// The same tile lists; tiles hold FP64 values, [row][rhs] with NR = 16 (at
+// most 16 right-hand sides in the pass) or 32 per row, rows padded to 16.
+struct Mm64Launch {
+    const RowDesc *rows;
+    const int32_t *items;
+    int64_t nitems;
+    const BlkDesc *blks;
+    const double *data;
+    const double *in_tree, *in_pts, *init;
+    double *out_tree, *out_pts;
+    double *Y;               // leaf phase: caller's column-major result
+    int64_t ldy;
+    int ncols;               // right-hand sides of the pass
+};
+hipError_t launch_mm64(const Mm64Launch &L, int phase, hipStream_t st);
+// Packs ncols right-hand sides of X (column-major, ldx) into FP64 point tiles.
+hipError_t launch_pack64(const double *X, int64_t ldx, int ncols, const int64_t *leaf_begin, const int64_t *leaf_end,
+                         int64_t nleaves, int64_t slot, double *tiles, hipStream_t st);
+
 // ---- batches of H^2 matrices (many right-hand sides, one launch per level slot)
 // Block offsets (BlkDesc.a) are absolute addresses; tile offsets index pool;
 // the leaf phase writes member m's result at Ytab[m] with leading dimension

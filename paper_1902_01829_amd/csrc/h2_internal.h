@@ -174,7 +174,8 @@ struct h2_matrix_ {
     int64_t nscales = 0;
     int64_t tile_slot = 0;            // elements per leaf in point tiles
     int64_t *d_leaf_begin = nullptr, *d_leaf_end = nullptr;
-    float *t_xh = nullptr, *t_yh = nullptr, *t_x = nullptr, *t_ynear = nullptr;   // tile workspace (lazy)
+    // tile workspace (lazy; FP32, or FP64 for FP64 matrices)
+    void *t_xh = nullptr, *t_yh = nullptr, *t_x = nullptr, *t_ynear = nullptr;
     // block loop chosen at the first pass of each tile width (32, or 16 for
     // passes of at most 16 right-hand sides)
     h2::MmConfig mm_cfg[2] = {{1, 0, 0}, {1, 0, 0}};

@@ -1509,3 +1509,5 @@ hipError_t launch_batch_pack(const PackEntry *entries, int64_t count, double con
 }
 
 }  // namespace h2
+
+#include "h2_mm64.h"

@@ -40,15 +40,19 @@ void run_lists(h2_matrix_ &A, const std::vector<WorkList> &lists, hipStream_t st
     }
 }
 
-// Tile workspace of the many-right-hand-side product, allocated at first use.
+// Tile workspace of the many-right-hand-side product, allocated at first use
+// (one allocation: none of it stays behind when memory runs out).
 void ensure_tiles(h2_matrix_ &A) {
     if (A.t_xh) return;
-    const int64_t kp = (A.st.rank + 15) / 16 * 16;
-    const int64_t tree = A.st.nnodes * kp * h2::MM_TILE, pts = (int64_t(1) << A.st.q) * A.tile_slot;
-    A.t_xh = static_cast<float *>(A.mem.alloc(tree * 4));
-    A.t_yh = static_cast<float *>(A.mem.alloc(tree * 4));
-    A.t_x = static_cast<float *>(A.mem.alloc(pts * 4));
-    A.t_ynear = static_cast<float *>(A.mem.alloc(pts * 4));
+    const int64_t vb = A.vec_f64 ? 8 : 4, kp = (A.st.rank + 15) / 16 * 16;
+    auto r256 = [](int64_t b) { return (b + 255) / 256 * 256; };
+    const int64_t tree = r256(A.st.nnodes * kp * h2::MM_TILE * vb);
+    const int64_t pts = r256((int64_t(1) << A.st.q) * A.tile_slot * vb);
+    char *p = static_cast<char *>(A.mem.alloc(2 * tree + 2 * pts));
+    A.t_xh = p;
+    A.t_yh = p + tree;
+    A.t_x = p + 2 * tree;
+    A.t_ynear = p + 2 * tree + pts;
 }
 
 }  // namespace
@@ -187,7 +191,8 @@ void run_tile_pass(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64
                    const h2::MmConfig &cfg, hipStream_t st) {
     const int64_t nleaves = int64_t(1) << A.st.q;
     {
-        check_hip(h2::launch_pack(X, ldx, j0, nrhs, A.d_leaf_begin, A.d_leaf_end, nleaves, A.tile_slot, A.t_x, st),
+        check_hip(h2::launch_pack(X, ldx, j0, nrhs, A.d_leaf_begin, A.d_leaf_end, nleaves, A.tile_slot,
+                                  static_cast<float *>(A.t_x), st),
                   "pack launch");
         run_lists(A, A.mm_lists, st, [&](const WorkList &w) {
             h2::MmLaunch L;
@@ -200,7 +205,7 @@ void run_tile_pass(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64
             L.data = w.data;
             L.scales = A.scales;
             L.in_tree = nullptr;
-            L.in_pts = A.t_x;
+            L.in_pts = static_cast<float *>(A.t_x);
             L.init = nullptr;
             L.out_tree = nullptr;
             L.out_pts = nullptr;
@@ -209,27 +214,75 @@ void run_tile_pass(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64
             L.ncols = std::min(h2::MM_TILE, nrhs - j0);
             switch (w.phase) {
                 case PH_UP:
-                    L.in_tree = A.t_xh;
-                    L.out_tree = A.t_xh;
+                    L.in_tree = static_cast<float *>(A.t_xh);
+                    L.out_tree = static_cast<float *>(A.t_xh);
                     break;
                 case PH_STREAM:
-                    L.in_tree = A.t_xh;
-                    L.out_tree = A.t_yh;
-                    L.out_pts = A.t_ynear;
+                    L.in_tree = static_cast<float *>(A.t_xh);
+                    L.out_tree = static_cast<float *>(A.t_yh);
+                    L.out_pts = static_cast<float *>(A.t_ynear);
                     break;
                 case PH_DOWN:
-                    L.in_tree = A.t_yh;
-                    L.init = A.t_yh;
-                    L.out_tree = A.t_yh;
+                    L.in_tree = static_cast<float *>(A.t_yh);
+                    L.init = static_cast<float *>(A.t_yh);
+                    L.out_tree = static_cast<float *>(A.t_yh);
                     break;
                 default:
-                    L.in_tree = A.t_yh;
-                    L.init = A.t_ynear;
+                    L.in_tree = static_cast<float *>(A.t_yh);
+                    L.init = static_cast<float *>(A.t_ynear);
                     break;
             }
             check_hip(h2::launch_mm(L, w.kind, int(w.phase), cfg, st), "mfma launch");
         });
     }
+}
+
+// Y = A X for an FP64 matrix on the FP64 matrix cores, MM_TILE right-hand
+// sides per pass (a pass of at most 16 takes 16-wide tiles).
+void run_tiles64(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t ldy, int nrhs, hipStream_t st) {
+    double *xh = static_cast<double *>(A.t_xh), *yh = static_cast<double *>(A.t_yh);
+    double *tx = static_cast<double *>(A.t_x), *tn = static_cast<double *>(A.t_ynear);
+    for (int j0 = 0; j0 < nrhs; j0 += h2::MM_TILE) {
+        const int ncols = std::min(h2::MM_TILE, nrhs - j0);
+        check_hip(h2::launch_pack64(X + int64_t(j0) * ldx, ldx, ncols, A.d_leaf_begin, A.d_leaf_end,
+                                    int64_t(1) << A.st.q, A.tile_slot, tx, st),
+                  "pack launch");
+        run_lists(A, A.mm_lists, st, [&](const WorkList &w) {
+            const bool sweep_down = w.phase == PH_DOWN || w.phase == PH_LEAF;
+            h2::Mm64Launch L;
+            L.rows = w.rows;
+            L.items = w.items;
+            L.nitems = w.nitems;
+            L.blks = w.blks;
+            L.data = static_cast<const double *>(w.data);
+            L.in_tree = sweep_down ? yh : xh;
+            L.in_pts = tx;
+            L.init = w.phase == PH_LEAF ? tn : yh;
+            L.out_tree = w.phase == PH_UP ? xh : yh;
+            L.out_pts = tn;
+            L.Y = Y + int64_t(j0) * ldy;
+            L.ldy = ldy;
+            L.ncols = ncols;
+            check_hip(h2::launch_mm64(L, int(w.phase), st), "fp64 mfma launch");
+        });
+    }
+}
+
+// Whether the FP64 tile workspace is there, allocated now if it can be: not
+// while the stream is being captured, and not when memory is short (the
+// product then runs column by column, in the handle's own workspace).
+bool tiles64_ready(h2_matrix_ &A, hipStream_t st) {
+    if (A.t_xh) return true;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    check_hip(hipStreamIsCapturing(st, &capture), "hipStreamIsCapturing");
+    if (capture != hipStreamCaptureStatusNone) return false;
+    try {
+        ensure_tiles(A);
+    } catch (const Failure &f) {
+        if (f.code != H2_ERR_OOM) throw;
+        return false;
+    }
+    return true;
 }
 
 // Y = A X on the matrix cores, MM_TILE right-hand sides per pass.
@@ -271,9 +324,11 @@ h2_status h2_matmat(h2_handle A, const double *X, int64_t ldx, double *Y, int64_
         if (nrhs < 1) fail(H2_ERR_INVALID_ARG, "nrhs must be >= 1");
         if (ldx < A->st.n || ldy < A->st.n) fail(H2_ERR_INVALID_ARG, "leading dimension below n");
         const hipStream_t st = static_cast<hipStream_t>(stream);
-        if (A->storage == H2_FP64 || A->half) {
-            // FP64 storage, or blocks stored by halves: one single-vector
-            // product per column
+        if (A->storage == H2_FP64 && !A->half && nrhs > 1 && tiles64_ready(*A, st)) {
+            run_tiles64(*A, X, ldx, Y, ldy, nrhs, st);
+        } else if (A->storage == H2_FP64 || A->half) {
+            // one right-hand side, no tile workspace, or blocks stored by
+            // halves: one single-vector product per column
             for (int j = 0; j < nrhs; ++j) run_product(*A, X + int64_t(j) * ldx, Y + int64_t(j) * ldy, st);
         } else {
             run_tiles(*A, X, ldx, Y, ldy, nrhs, st);
