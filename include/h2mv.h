@@ -79,7 +79,9 @@ typedef enum { H2_FP64 = 0, H2_FP32 = 1, H2_BF16_SCALED = 2 } h2_storage;
  * stored bytes in bytes_coupling and bytes_dense.  Handles stored by halves
  * are rejected with UNSUPPORTED by h2_orthogonalize, h2_compress,
  * h2_transpose (such a matrix is its own transpose) and h2_batch_create;
- * h2_matmat runs one single-vector product per column. */
+ * h2_matmat reads every stored block twice on H2_FP64 handles (as itself and
+ * as its transpose) and runs one single-vector product per column on the
+ * others. */
 #define H2_HALF_STORAGE 16
 
 /* flags */
@@ -330,8 +332,8 @@ h2_status h2_set_schedule(h2_handle A, int schedule, int near_wg_per_cu, double 
  * dense contraction.
  *  X  device, column-major n x nrhs, leading dimension ldx >= n, tree order.
  *  Y  device, column-major n x nrhs, leading dimension ldy >= n.
- * Handles stored by halves, and calls with one right-hand side on H2_FP64
- * handles, run nrhs single-vector products; the others run on the matrix cores,
+ * Handles stored by halves in reduced storage, and calls with one right-hand
+ * side on H2_FP64 handles, run nrhs single-vector products; the others run on the matrix cores,
  * 32 right-hand sides per pass (FP64 MFMA and FP64 sums for H2_FP64, FP32 MFMA
  * for H2_FP32 and H2_BF16_SCALED).  The first such call on a handle allocates
  * the tiles (two per tree node and two per leaf); on an H2_FP64 handle a call

@@ -602,7 +602,42 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
                 if (fi >= 0) add_blk(fill[fi].a, int32_t(s.size(lf + t)), fill[fi].sidx, true, t);
             }
         }
+        // Stored by halves, FP64, many right-hand sides: rows with all their
+        // blocks, a mirrored one marked (sidx = 1) and pointing at the stored
+        // block; the spatial order of the full storage's tile list.  Encoded
+        // on a second host thread (it reads the structure only).
+        auto half_tiles = [&] {
+            Encoded e;
+            e.rows.reserve(size_t(2 * s.nnodes));
+            e.blks.reserve(size_t(total));
+            auto add = [&](const h2::Bsr &B, int64_t i, int64_t base, bool point, int64_t id, int R) {
+                RowDesc d;
+                d.out = mm_off(point, id);
+                d.init = -1;
+                d.b0 = int32_t(e.blks.size());
+                for (int32_t b = B.rowptr[i]; b < B.rowptr[i + 1]; ++b) {
+                    const int64_t st = A.blk_store[size_t(base + b)];
+                    const int64_t t = B.colidx[b], in = point ? t : id - i + t;
+                    e.blks.push_back({fill[size_t(st >= 0 ? st : -st - 1)].a, mm_off(point, in),
+                                      point ? int32_t(s.size(lf + t)) : R, st >= 0 ? 0 : 1});
+                }
+                d.b1 = int32_t(e.blks.size());
+                d.R = R;
+                d.sel = point ? h2::ROW_IN_X | h2::ROW_OUT_P : 0;
+                e.rows.push_back(d);
+            };
+            std::vector<int64_t> base(size_t(q) + 2, 0);   // first block of every level in the lists, then of the dense ones
+            for (int l = 0; l <= q; ++l) base[size_t(l) + 1] = base[size_t(l)] + s.coupling[l].blocks();
+            for (int64_t i = 0; i < nleaves; ++i) add(s.dense, i, base[size_t(q) + 1], true, i, int(s.size(lf + i)));
+            for (int l = q; l >= s.lmin && lowrank; --l)
+                for (int64_t i = 0; i < (int64_t(1) << l); ++i)
+                    add(s.coupling[l], i, base[size_t(l)], false, Structure::first(l) + i, kl[l]);
+            e.items = wave_items(e.rows, e.blks);
+            return e;
+        };
         if (A.half) {
+            std::future<Encoded> tiles;
+            if (A.vec_f64) tiles = std::async(std::launch::async | std::launch::deferred, half_tiles);
             // One launch reads every stored block once for both of its
             // products.  Its wavefronts take groups of up to HALF_GROUP_ROWS
             // consecutive block rows of one kind (the list's spatial order:
@@ -774,6 +809,7 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             w.partials_bytes = int64_t(ents.size()) * 64 * (A.vec_f64 ? 8 : 4);
             w.partials = A.mem.alloc(w.partials_bytes);
             A.lists.push_back(w);
+            if (tiles.valid()) commit(1, PH_STREAM, sk, A.blocks, tiles.get());
             clear();
         }
     }

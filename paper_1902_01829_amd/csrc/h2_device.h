@@ -212,6 +212,8 @@ struct Mm64Launch {
     double *Y;               // leaf phase: caller's column-major result
     int64_t ldy;
     int ncols;               // right-hand sides of the pass
+    bool half;               // streaming list of a matrix stored by halves: every block of a row
+                             // listed, BlkDesc.sidx = 1 where the stored block is its transpose
 };
 hipError_t launch_mm64(const Mm64Launch &L, int phase, hipStream_t st);
 // Packs ncols right-hand sides of X (column-major, ldx) into FP64 point tiles.

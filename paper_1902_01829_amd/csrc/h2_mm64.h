@@ -50,8 +50,20 @@ struct Chunk {
     f64x2 a[2];
     typename Rhs<NR>::V b[2];
     int left;   // columns of the block from this chunk on
+    int tr;     // HALF: the block is the transpose of the stored one
 };
 
+// HALF (streaming launch of a matrix stored by halves): blocks with sidx = 1
+// are the transposes of the stored ones.  A 16-byte item then holds two rows
+// of the product's block at one column, where otherwise it holds two columns
+// at one row, so the item's two row tiles take the even and the odd rows for
+// either kind, and a chunk's two loads per lane are the items of columns
+// 4 u + g (transposed) or of rows 2 n + t (as stored).  Every stored block is
+// read twice, as itself and as its mirror: writing the mirror's product out
+// instead would cost as many bytes in partial tiles as the second read.
+// (60,000 2-D points of rank 49, 6 right-hand sides 1.98 -> 0.75 ms against
+// single-vector products; 2^18 points of rank 64, 32 of them 37.1 -> 3.4 ms.)
+//
 // SPLIT = 4: the four wavefronts of a workgroup take a quarter of one item's
 // chunks each, and the first adds the others' sums in order through LDS.
 //
@@ -63,7 +75,7 @@ struct Chunk {
 // loads carry no condition (past the last chunk they re-read it), which keeps
 // the compiler's wait counts exact.  Sums run in FP64 accumulators over all
 // blocks of the row, in block order.
-template <int NR, bool LEAF, int D, int SPLIT>
+template <int NR, bool LEAF, int D, int SPLIT, bool HALF>
 __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__restrict__ rows,
                                           const BlkDesc *__restrict__ blks, int32_t item, int wv, int lane) {
     constexpr int NN = NR / 16;   // MFMA column tiles
@@ -71,11 +83,11 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
     const RowDesc rd = rows[item >> 1];
     const int R = rd.R, mt = item & 1, n = lane & 15, g = lane >> 4;
     if (32 * mt >= R) return;
-    const bool two = 32 * mt + 16 < R;   // wave-uniform: the item has a second row tile
+    const bool two = HALF ? 32 * mt + 1 < R : 32 * mt + 16 < R;   // wave-uniform: the item has a second row tile
     int rc[2];
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        const int r = 32 * mt + 16 * t + n;
+        const int r = 32 * mt + (HALF ? 2 * n + t : 16 * t + n);
         rc[t] = r < R ? r : R - 1;   // rows past the segment read its last row; their sums are not used
     }
     const double *xbase = (rd.sel & ROW_IN_X) ? L.in_pts : L.in_tree;
@@ -85,19 +97,21 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
     if (nb > 0) {
         const BlkDesc my = blks[rd.b0 + (lane < nb ? lane : nb - 1)];   // one descriptor per lane
         const char *pa = nullptr, *pb = nullptr;                         // the block and its input tile
-        int C = 0, c0 = 0, k = 0;
+        int C = 0, c0 = 0, k = 0, tr = 0;
         auto open = [&](int kk) {
             BlkDesc d;
             if (kk < 64) {
                 d.a = readlane64(my.a, kk);
                 d.in = readlane64(my.in, kk);
                 d.C = __builtin_amdgcn_readlane(my.C, kk);
+                if constexpr (HALF) d.sidx = __builtin_amdgcn_readlane(my.sidx, kk);
             } else {
                 d = blks[rd.b0 + kk];
             }
             pa = reinterpret_cast<const char *>(static_cast<const double *>(L.data) + d.a);
             pb = reinterpret_cast<const char *>(xbase + d.in);
             C = d.C;
+            if constexpr (HALF) tr = d.sidx;
         };
         // the row's chunks, counted first: whole rounds of the ring then hold no
         // branch around a load (the compiler's waits would become full drains)
@@ -134,15 +148,22 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
         open(k);
         auto load = [&](Chunk<NR> &ch) {
             ch.left = C - c0;
+            ch.tr = tr;
             const int CW = (C + 1) >> 1, cg = (c0 >> 1) + g, cgc = cg < CW ? cg : CW - 1;
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
-                ch.a[t] = __builtin_nontemporal_load(
-                    reinterpret_cast<const f64x2 *>(pa + uint32_t(cgc * R + rc[t]) * 16u));
+            for (int t = 0; t < 2; ++t) {
+                int at = cgc * R + rc[t];
+                if constexpr (HALF) {   // stored block: C rows, R columns
+                    const int kk = c0 + 4 * t + g;
+                    at = tr ? (rc[0] >> 1) * C + (kk < C ? kk : C - 1) : at;
+                }
+                ch.a[t] = __builtin_nontemporal_load(reinterpret_cast<const f64x2 *>(pa + uint32_t(at) * 16u));
+            }
             // (tile rows up to the next multiple of 16 exist and are zero)
-            const uint32_t ob = uint32_t((c0 + 2 * g) * NR + n * NN) * 8u;
+            const int row = c0 + (HALF && tr ? g : 2 * g), step = HALF && tr ? 4 * NR * 8 : NR * 8;
+            const uint32_t ob = uint32_t(row * NR + n * NN) * 8u;
 #pragma unroll
-            for (int t = 0; t < 2; ++t) ch.b[t] = *reinterpret_cast<const B *>(pb + ob + uint32_t(t * NR * 8));
+            for (int t = 0; t < 2; ++t) ch.b[t] = *reinterpret_cast<const B *>(pb + ob + uint32_t(t * step));
             if (k < nb) {   // (wave-uniform; past the last chunk it is loaded again)
                 if (c0 + 8 < C) {
                     c0 += 8;
@@ -157,6 +178,20 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
         for (int s = 0; s < D; ++s) load(ring[s]);
         auto products = [&](const Chunk<NR> &ch) {
             f64x2 a[2] = {ch.a[0], ch.a[1]};
+            auto step = [&](int u, int t, double v) {
+#pragma unroll
+                for (int j = 0; j < NN; ++j)
+                    acc[t][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(v, Rhs<NR>::get(ch.b[u], j), acc[t][j], 0, 0, 0);
+            };
+            if (HALF && ch.tr) {   // wave-uniform
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    if (4 * u + g >= ch.left) a[u] = f64x2{0.0, 0.0};   // columns past the block's width
+                    step(u, 0, a[u].x);
+                    step(u, 1, a[u].y);
+                }
+                return;
+            }
             if (ch.left < 8 && 2 * g >= ch.left) {   // a block's last chunk: column pairs past its width
                 a[0] = f64x2{0.0, 0.0};
                 a[1] = f64x2{0.0, 0.0};
@@ -164,13 +199,8 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    if (t && !two) break;
-#pragma unroll
-                    for (int j = 0; j < NN; ++j)
-                        acc[t][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(u ? a[t].y : a[t].x, Rhs<NR>::get(ch.b[u], j),
-                                                                         acc[t][j], 0, 0, 0);
-                }
+                for (int t = 0; t < 2; ++t)
+                    if (t == 0 || two) step(u, t, u ? a[t].y : a[t].x);
         };
         int i = 0;
         for (; i + D <= nch; i += D) {
@@ -203,22 +233,24 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
                 for (int j = 0; j < NN; ++j) acc[t][j] += part[w][t * NN + j][lane];
     }
 
-    // Lane (g, n) holds rows 32 mt + 16 t + g + 4 e of right-hand sides NN n + j.
+    // Lane (g, n) holds rows 32 mt + 16 t + g + 4 e (HALF: 32 mt + 2 (g + 4 e) + t)
+    // of right-hand sides NN n + j.
     const int Rp = round16(R);
+    auto out_row = [&](int t, int e) { return 32 * mt + (HALF ? 2 * (g + 4 * e) + t : 16 * t + g + 4 * e); };
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
-        if (t && !two) break;
+        if (!HALF && t && !two) break;   // (HALF: its padding rows are odd ones too)
         B init[4] = {};
         if (LEAF || rd.init >= 0) {   // requested for all rows before any store
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const int r = 32 * mt + 16 * t + g + 4 * e;
+                const int r = out_row(t, e);
                 init[e] = *reinterpret_cast<const B *>(L.init + rd.init + int64_t(r) * NR + n * NN);
             }
         }
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            const int r = 32 * mt + 16 * t + g + 4 * e;
+            const int r = out_row(t, e);
             if (r >= Rp) continue;
             B v;
             if constexpr (NR == 32) v = init[e] + f64x2{acc[t][0][e], acc[t][NN - 1][e]};
@@ -239,19 +271,20 @@ __device__ __forceinline__ void mm64_item(const Mm64Launch &L, const RowDesc *__
 // One wavefront per work item, four per workgroup, in the dispatch order laid
 // out by the host (h2_device.h), or one workgroup per item (SPLIT); one
 // kernel name per phase.
-#define H2_MM64_KERNEL(NAME, LEAF)                                                                              \
+#define H2_MM64_KERNEL(NAME, LEAF, HALF)                                                                             \
     template <int NR, int D, int SPLIT>                                                                        \
     __global__ __launch_bounds__(256) void NAME(Mm64Launch L, const RowDesc *__restrict__ rows,                 \
                                                 const BlkDesc *__restrict__ blks) {                            \
         const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;              \
         const int64_t i = SPLIT > 1 ? int64_t(blockIdx.x) : int64_t(blockIdx.x) * 4 + wv;                      \
         const int32_t it = __builtin_amdgcn_readfirstlane(L.items[i]);                                         \
-        if (it >= 0) mm64_item<NR, LEAF, D, SPLIT>(L, rows, blks, it, wv, lane);                               \
+        if (it >= 0) mm64_item<NR, LEAF, D, SPLIT, HALF>(L, rows, blks, it, wv, lane);                               \
     }
-H2_MM64_KERNEL(mm64_upsweep_kernel, false)
-H2_MM64_KERNEL(mm64_stream_kernel, false)
-H2_MM64_KERNEL(mm64_downsweep_kernel, false)
-H2_MM64_KERNEL(mm64_leafexpand_kernel, true)
+H2_MM64_KERNEL(mm64_upsweep_kernel, false, false)
+H2_MM64_KERNEL(mm64_stream_kernel, false, false)
+H2_MM64_KERNEL(mm64_stream_half_kernel, false, true)
+H2_MM64_KERNEL(mm64_downsweep_kernel, false, false)
+H2_MM64_KERNEL(mm64_leafexpand_kernel, true, false)
 #undef H2_MM64_KERNEL
 
 // Right-hand sides j0 .. of the caller's column-major X into point tiles, a
@@ -296,7 +329,10 @@ void launch_phase64(const Mm64Launch &L, int phase, hipStream_t st) {
     const dim3 grid(unsigned(SPLIT > 1 ? L.nitems : L.nitems / 4)), block(256);
     switch (phase) {
     case PHASE_UP: hipLaunchKernelGGL((mm64_upsweep_kernel<NR, D, SPLIT>), grid, block, 0, st, L, L.rows, L.blks); break;
-    case PHASE_STREAM: hipLaunchKernelGGL((mm64_stream_kernel<NR, D, SPLIT>), grid, block, 0, st, L, L.rows, L.blks); break;
+    case PHASE_STREAM:
+        if (L.half) hipLaunchKernelGGL((mm64_stream_half_kernel<NR, D, SPLIT>), grid, block, 0, st, L, L.rows, L.blks);
+        else hipLaunchKernelGGL((mm64_stream_kernel<NR, D, SPLIT>), grid, block, 0, st, L, L.rows, L.blks);
+        break;
     case PHASE_DOWN: hipLaunchKernelGGL((mm64_downsweep_kernel<NR, D, SPLIT>), grid, block, 0, st, L, L.rows, L.blks); break;
     default: hipLaunchKernelGGL((mm64_leafexpand_kernel<NR, D, SPLIT>), grid, block, 0, st, L, L.rows, L.blks); break;
     }

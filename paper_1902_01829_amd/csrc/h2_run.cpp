@@ -237,6 +237,14 @@ void run_tile_pass(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64
     }
 }
 
+// Fewest right-hand sides a pass on the FP64 matrix cores is used for.  A pass
+// of up to 16 costs 1.1 to 1.5 single-vector products (2-D, 2^18 points 2.27
+// against 1.79 ms, 60,000 points of rank 49 0.57 against 0.39 ms); stored by
+// halves it reads every block twice, where the single-vector product reads it
+// once, and costs 2.2 to 2.6 of them from 60,000 points up (2.94 against 1.16
+// ms, 0.74 against 0.34 ms).
+int least_columns64(const h2_matrix_ &A) { return A.half ? 3 : 2; }
+
 // Y = A X for an FP64 matrix on the FP64 matrix cores, MM_TILE right-hand
 // sides per pass (a pass of at most 16 takes 16-wide tiles).
 void run_tiles64(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t ldy, int nrhs, hipStream_t st) {
@@ -244,6 +252,10 @@ void run_tiles64(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t
     double *tx = static_cast<double *>(A.t_x), *tn = static_cast<double *>(A.t_ynear);
     for (int j0 = 0; j0 < nrhs; j0 += h2::MM_TILE) {
         const int ncols = std::min(h2::MM_TILE, nrhs - j0);
+        if (ncols < least_columns64(A)) {   // the last pass
+            for (int j = j0; j < nrhs; ++j) run_product(A, X + int64_t(j) * ldx, Y + int64_t(j) * ldy, st);
+            break;
+        }
         check_hip(h2::launch_pack64(X + int64_t(j0) * ldx, ldx, ncols, A.d_leaf_begin, A.d_leaf_end,
                                     int64_t(1) << A.st.q, A.tile_slot, tx, st),
                   "pack launch");
@@ -263,6 +275,7 @@ void run_tiles64(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t
             L.Y = Y + int64_t(j0) * ldy;
             L.ldy = ldy;
             L.ncols = ncols;
+            L.half = A.half && w.phase == PH_STREAM;
             check_hip(h2::launch_mm64(L, int(w.phase), st), "fp64 mfma launch");
         });
     }
@@ -324,11 +337,11 @@ h2_status h2_matmat(h2_handle A, const double *X, int64_t ldx, double *Y, int64_
         if (nrhs < 1) fail(H2_ERR_INVALID_ARG, "nrhs must be >= 1");
         if (ldx < A->st.n || ldy < A->st.n) fail(H2_ERR_INVALID_ARG, "leading dimension below n");
         const hipStream_t st = static_cast<hipStream_t>(stream);
-        if (A->storage == H2_FP64 && !A->half && nrhs > 1 && tiles64_ready(*A, st)) {
+        if (A->vec_f64 && nrhs >= least_columns64(*A) && tiles64_ready(*A, st)) {
             run_tiles64(*A, X, ldx, Y, ldy, nrhs, st);
-        } else if (A->storage == H2_FP64 || A->half) {
-            // one right-hand side, no tile workspace, or blocks stored by
-            // halves: one single-vector product per column
+        } else if (A->vec_f64 || A->half) {
+            // too few right-hand sides, no tile workspace, or blocks stored by
+            // halves in reduced storage: one single-vector product per column
             for (int j = 0; j < nrhs; ++j) run_product(*A, X + int64_t(j) * ldx, Y + int64_t(j) * ldy, st);
         } else {
             run_tiles(*A, X, ldx, Y, ldy, nrhs, st);

@@ -24,16 +24,17 @@ CASES = [
 ]
 
 
-def _build(n, dim, leaf, p):
+def _build(n, dim, leaf, p, half=False):
     from paper_1902_01829_amd import h2mv
     pts = np.random.default_rng(n).random((n, dim))
-    return h2mv.H2Matrix(pts, dim, leaf, p, 0.9, 0.1)
+    return h2mv.H2Matrix(pts, dim, leaf, p, 0.9, 0.1, storage=h2mv.H2_HALF_STORAGE if half else 0)
 
 
+@pytest.mark.parametrize("half", [False, True], ids=["full", "half"])
 @pytest.mark.parametrize("n,dim,leaf,p,nrhs", CASES)
-def test_columns_match_single_products(n, dim, leaf, p, nrhs):
-    print(f"case n={n} dim={dim} leaf={leaf} p={p} nrhs={nrhs}", flush=True)
-    A = _build(n, dim, leaf, p)
+def test_columns_match_single_products(n, dim, leaf, p, nrhs, half):
+    print(f"case n={n} dim={dim} leaf={leaf} p={p} nrhs={nrhs} half={half}", flush=True)
+    A = _build(n, dim, leaf, p, half)
     X = torch.randn(nrhs, n, dtype=torch.float64, device="cuda")
     Y = A.matmat(X)
     assert torch.equal(Y, A.matmat(X))   # the sums keep their order from call to call
