@@ -481,6 +481,13 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
     auto mm_off = [&](bool point, int64_t id) { return point ? id * A.tile_slot : id * kp * h2::MM_TILE; };
     // enc 0: single-vector offsets into A.lists; enc 1: tile offsets into A.mm_lists.
     // Rows in the order of `order` (indices into L), else in L's order.
+    // Single-vector streaming rows carry their number of steps (h2_device.h).
+    auto stream_sel = [&](int sel, int R, const BlkDesc *b, const BlkDesc *e) {
+        const int gw = (64 / R) * (16 / h2::elem_bytes(sk));
+        int64_t steps = 0;
+        for (; b < e; ++b) steps += (b->C + gw - 1) / gw;
+        return steps < (int64_t(1) << 23) ? sel | int(steps << 8) : sel;
+    };
     // encode only reads L and the pool (two encodings may run at once);
     // commit uploads and records the list.
     struct Encoded {
@@ -513,6 +520,8 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             d.b1 = int32_t(e.blks.size());
             d.R = r.R;
             d.sel = r.sel;
+            if (enc == 0 && ph == PH_STREAM)
+                d.sel = stream_sel(r.sel, r.R, e.blks.data() + d.b0, e.blks.data() + d.b1);
             e.rows.push_back(d);
         }
         if (enc == 1) {
@@ -836,7 +845,9 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
         std::iota(by_len.begin(), by_len.end(), size_t(0));
         std::stable_sort(by_len.begin(), by_len.end(), [&](size_t a, size_t b) { return L[a].nb() > L[b].nb(); });
         const int64_t nblk = int64_t(pool.size());
-        const bool split = int64_t(L.size()) < kSplitRows && nblk > int64_t(L.size());
+        // about 8 blocks per piece, within kSplitWaves .. kMaxSplitWaves pieces
+        const int64_t pieces = std::min(std::max(nblk / 8, kSplitWaves), kMaxSplitWaves);
+        const bool split = 2 * pieces >= 3 * int64_t(L.size()) && nblk > int64_t(L.size());
         Encoded single;
         if (!split) single = encode(0, PH_STREAM, &by_len);
         commit(1, PH_STREAM, sk, A.blocks, tiles.get());
@@ -855,9 +866,9 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             if (L[r].point) order.push_back(r);
         std::vector<int64_t> near_cum{0};
         if (split) {
-            // few rows: every row cut into chunks of `chunk` blocks, one wavefront
-            // each, writing FP64 partial sums that a second launch adds up per row
-            const int chunk = int(std::max<int64_t>(1, (nblk + kSplitWaves - 1) / kSplitWaves));
+            // few rows: every row cut into chunks of at most `chunk` blocks, one
+            // wavefront each, writing FP64 partial sums that a second launch adds up per row
+            const int chunk = int(std::max<int64_t>(1, (nblk + pieces - 1) / pieces));
             std::vector<RowDesc> rows;
             std::vector<BlkDesc> blks;
             std::vector<h2::ReduceDesc> red;
@@ -867,18 +878,19 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
                 const int nb = int(r.nb()), nc = std::max(1, (nb + chunk - 1) / chunk);
                 red.push_back({mv_off(r.point, r.id), int32_t(rows.size()), int32_t(rows.size() + nc), r.R,
                                r.point ? 1 : 0});
-                for (int c = 0; c < nc; ++c) {
+                for (int c = 0; c < nc; ++c) {   // pieces of about equal length
                     RowDesc d;
                     d.out = int64_t(rows.size()) * 64;
                     d.init = -1;
                     d.R = r.R;
                     d.sel = (r.sel & h2::ROW_IN_X) | h2::ROW_OUT_P;
                     d.b0 = int32_t(blks.size());
-                    for (int b = c * chunk; b < std::min(nb, (c + 1) * chunk); ++b) {
+                    for (int b = int(int64_t(nb) * c / nc); b < int(int64_t(nb) * (c + 1) / nc); ++b) {
                         const LBlk &lb = pool[r.b0 + size_t(b)];
                         blks.push_back({lb.a, mv_off(lb.point, lb.id), lb.C, lb.sidx});
                     }
                     d.b1 = int32_t(blks.size());
+                    d.sel = stream_sel(d.sel, d.R, blks.data() + d.b0, blks.data() + d.b1);
                     rows.push_back(d);
                 }
             }
@@ -911,23 +923,13 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             w.near_cum = std::move(near_cum);
             A.lists.push_back(w);
         } else {
-            commit(0, PH_STREAM, sk, A.blocks, std::move(single));
-            std::vector<int64_t> b0(L.size() + 1, 0);
-            for (size_t r = 0; r < L.size(); ++r) b0[r + 1] = b0[r] + int64_t(L[r].nb());
-            std::vector<RowDesc> srows;
+            std::vector<RowDesc> srows;   // (the rows of L, now in by_len order)
             srows.reserve(L.size());
             for (size_t o = 0; o < order.size(); ++o) {
-                const LRow &r = L[order[o]];
-                RowDesc d;
-                d.out = mv_off(r.point, r.id);
-                d.init = -1;
-                d.b0 = int32_t(b0[order[o]]);
-                d.b1 = int32_t(b0[order[o] + 1]);
-                d.R = r.R;
-                d.sel = r.sel;
-                srows.push_back(d);
-                if (int64_t(o) >= ncoup) near_cum.push_back(near_cum.back() + int64_t(r.nb()));
+                srows.push_back(single.rows[order[o]]);
+                if (int64_t(o) >= ncoup) near_cum.push_back(near_cum.back() + int64_t(L[order[o]].nb()));
             }
+            commit(0, PH_STREAM, sk, A.blocks, std::move(single));
             WorkList &w = A.lists.back();
             w.srows = A.mem.upload(srows, stream);
             w.nsrows_coupling = ncoup;

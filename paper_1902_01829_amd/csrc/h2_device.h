@@ -24,7 +24,10 @@ struct RowDesc {
     int64_t init;   // element offset of the segment added to the result, or -1
     int32_t b0, b1; // blocks [b0, b1) of the block list
     int32_t R;      // rows of the segment (<= 64)
-    int32_t sel;    // ROW_IN_X: input is the point vector; ROW_OUT_P: output is the point vector
+    int32_t sel;    // ROW_IN_X: input is the point vector; ROW_OUT_P: output is the point vector.
+                    // Above the low 8 bits: in batches the member; in single-vector streaming lists the
+                    // row's number of steps, the sum over its blocks of ceil(C / (G W)), G = 64 / R lane
+                    // groups of W columns per item (0: not known)
 };
 enum { ROW_IN_X = 1, ROW_OUT_P = 2 };
 

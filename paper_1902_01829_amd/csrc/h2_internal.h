@@ -130,10 +130,17 @@ struct WorkList {
     std::vector<int64_t> near_cum;   // blocks of the near-field rows of srows, cumulative (size rows + 1)
 };
 
-// A single-vector stream list with fewer block rows than this is split into
-// chunks: one wavefront per row would leave most of the machine idle.
-constexpr int64_t kSplitRows = 4096;
-constexpr int64_t kSplitWaves = 4096;   // target number of chunks (about 16 per CU)
+// A single-vector stream list with fewer than two thirds as many block rows as
+// the pieces it can be cut into is cut: one wavefront per row would leave the
+// machine idle, at the end of the launch if not throughout (5,120 FP64
+// wavefronts run at once).  Pieces hold about 8 blocks, 4,096 to 16,384 of them.
+// Measured, single-vector product: 50,000 3-D points of rank 27, 6,143 rows
+// of 90 blocks, uncut / 16,384 / 65,536 pieces 675 / 614 / 628 us (FP64), 298 /
+// 240 / 262 (BF16); 20,011 points 4,096 / 16,384 pieces 272 / 235 us; 16,384
+// 2-D points of rank 64 (16,800 blocks) 4,096 / 8,192 / 16,384 pieces 152 / 155
+// / 162 us; 100,000 2-D points of rank 25 (12,287 rows) uncut / 16,384 pieces
+// 360 / 372 us.
+constexpr int64_t kSplitWaves = 4096, kMaxSplitWaves = 16384;
 
 // ---------------------------------------------------------------- batches
 // Many H^2 matrices of uneven size and rank per launch: the members' tile

@@ -107,6 +107,12 @@ template <> struct Elem<ELEM_BF16> {
     }
 };
 
+__device__ inline int64_t readlane64(int64_t v, int j) {
+    const uint32_t lo = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(uint64_t(v))), j));
+    const uint32_t hi = uint32_t(__builtin_amdgcn_readlane(int(uint32_t(uint64_t(v) >> 32)), j));
+    return int64_t((uint64_t(hi) << 32) | lo);
+}
+
 // Decodes element index e of an R-row block in 16-byte column groups of W.
 __device__ inline void decode(int e, int R, int W, int &r, int &c) {
     const int w = e % W, t = e / W;
@@ -298,19 +304,16 @@ __global__ __launch_bounds__(256) void transpose_blocks_kernel(const T *__restri
 }
 
 // ---------------------------------------------------------------- block-row product
-// One wavefront per output segment.  For every block of the row, the input
-// segment (<= 64 values) is staged in the wave's LDS slot; each lane then
-// streams its row's 16-byte items of the block with non-temporal loads and
-// accumulates the block's dot products.  One block's partial sum is kept in
-// the block arithmetic type, sums over blocks in FP64.
-// ONE_ROUND (the tree sweeps and the leaf launch, whose rows hold one or two
-// blocks): all of a lane's items of a block are requested at once, before
-// the input segment, so a block costs one memory round trip instead of one
-// per eight items; on the few rows of the levels near the root that chain is
-// the launch's whole duration.  The streaming launch's rows hold many blocks
-// and keep eight items in flight per round, which leaves room for more
-// wavefronts per SIMD.  Both take the same products in the same order.
-template <int KIND, typename TV, typename TO1, bool ONE_ROUND>
+// Tree sweeps and leaf launch: one wavefront per output segment, whose row
+// holds one or two blocks.  The block's input segment (<= 64 values) is staged
+// in the wave's LDS slot; each lane streams its row's 16-byte items of the
+// block with non-temporal loads and accumulates the block's dot products.  One
+// block's partial sum is kept in the block arithmetic type, sums over blocks
+// in FP64.  All of a lane's items of a block of at most 8 per lane are requested
+// at once, before the input segment, so the block costs one memory round trip
+// instead of one per eight items; on the few rows of the levels near the root
+// that chain is the launch's whole duration.
+template <int KIND, typename TV, typename TO1>
 __device__ __forceinline__ void blockrow_body(
     const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,
     const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales,
@@ -321,10 +324,10 @@ __device__ __forceinline__ void blockrow_body(
     constexpr int W = E::W;
     __shared__ __attribute__((aligned(16))) P xs[4][64];
     __shared__ double red[4][64];
-    // ONE_ROUND: the wave index made uniform, so that the row and block
-    // descriptors come through scalar loads and a block's base address is
-    // uniform (its loads then take 32-bit lane offsets)
-    const int wv = ONE_ROUND ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    // the wave index made uniform, so that the row and block descriptors come
+    // through scalar loads and a block's base address is uniform (its loads
+    // then take 32-bit lane offsets)
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
     const int64_t row = int64_t(blockIdx.x) * 4 + wv;
     if (row >= nrows) return;
@@ -338,7 +341,7 @@ __device__ __forceinline__ void blockrow_body(
         using V = typename E::V;
         P part = P(0);
         bool done = false;
-        if constexpr (ONE_ROUND) {
+        {
             // Blocks of at most 8 items per lane: N items, a compile-time
             // count (the smallest of 2, 4, 8 covering the block's ceil(CW / G)
             // column groups per lane, a wave-uniform choice), so that they
@@ -437,22 +440,209 @@ __device__ __forceinline__ void blockrow_body(
     }
 }
 
+// ---------------------------------------------------------------- streaming launch
+// One wavefront per row (or chunk of a row), lane = grp * R + r: lane group
+// grp < G = 64 / R takes the block's column groups grp, grp + G, ... of row r.
+// A row is walked as one sequence of steps -- in step t of a block every lane
+// takes item t of its column groups -- through a ring of D steps held in
+// registers, refilled as they are used, so D steps' loads stay in flight
+// across block boundaries.  (Waiting at every block's end for its input, then
+// for its items eight at a time, left blocks of a few KiB latency-bound: three
+// dependent round trips each.)  Of the input segment a step loads only the
+// G W values it multiplies, one per lane, and shares them through the
+// wavefront's LDS slot.  Bound by the HBM for large matrices (2^20 points: 6.9
+// TB/s as before); the product of 50,000 3-D points of rank 27 with leaves of
+// 24-25 points went from 1239 to 610 us in FP64, 745 to 350 in FP32 and 559 to
+// 240 in BF16.  The loads carry no condition (addresses are clamped
+// into the block, past the last step it is loaded again), so the compiler's
+// waits count them exactly.  One block's partial sum is kept in the block
+// arithmetic type, sums over blocks in FP64, in block order.
+template <int KIND, typename TV, typename TO1, int D>
+__device__ __forceinline__ void stream_body(
+    const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,
+    const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales,
+    const TV *__restrict__ in0, const double *__restrict__ in1, TV *__restrict__ out0, TO1 *__restrict__ out1) {
+    using E = Elem<KIND>;
+    using P = typename E::P;
+    using V = typename E::V;
+    constexpr int W = E::W;
+    __shared__ __attribute__((aligned(16))) P xs[4][64];
+    __shared__ double red[4][64];
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t row = int64_t(blockIdx.x) * 4 + wv;
+    if (row >= nrows) return;
+    const RowDesc rd = rows[row];
+    const int R = rd.R, G = 64 / R, g0 = lane / R, rr = lane - g0 * R;
+    const int grp = g0 < G ? g0 : 0;   // lanes past the last group repeat the first one's loads; their sums are not used
+    const int nb = rd.b1 - rd.b0;
+    double acc = 0.0;
+    if (nb > 0) {   // wave-uniform
+        const BlkDesc first = blks[rd.b0];
+        BlkDesc my = blks[rd.b0 + (lane < nb ? lane : nb - 1)];   // descriptors of 64 blocks, one per lane
+        float sc = 1.0f;
+        if constexpr (KIND == ELEM_BF16) sc = scales[my.sidx];
+        const int gw = G * W;
+        int nsteps = rd.sel >> 8;
+        if (nsteps == 0) {
+            for (int k = lane; k < nb; k += 64) nsteps += (blks[rd.b0 + k].C + gw - 1) / gw;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) nsteps += __shfl_xor(nsteps, o);
+            nsteps = __builtin_amdgcn_readfirstlane(nsteps);
+        }
+        const double *in64 = in1;   // the FP64 input: x, or x^ of an FP64 matrix
+        if constexpr (std::is_same<TV, double>::value) {
+            if (!(rd.sel & ROW_IN_X)) in64 = in0;
+        }
+        auto steps = [&](auto input_is_x) __attribute__((always_inline)) {
+            constexpr bool IN_X = decltype(input_is_x)::value;
+            using TX = std::conditional_t<IN_X, double, TV>;
+            const TX *xbase;
+            if constexpr (IN_X) xbase = in64;
+            else xbase = in0;
+            struct Step {
+                V a;
+                TX x;
+                int left;     // columns of the block from this step on
+                float scale;  // BF16
+            };
+            // the next step to load: its block and input segment, the lane's byte
+            // offsets in them with their last valid values, the columns left
+            const char *pa = nullptr, *px = nullptr;
+            uint32_t oa = 0, oa_last = 0, ox = 0, ox_last = 0;
+            int left = 0, k = 0;
+            float scale = 1.0f;
+            const uint32_t oa0 = uint32_t(grp * R + rr) * 16u, oa_step = uint32_t(G * R) * 16u;
+            const uint32_t ox0 = uint32_t(min(lane, gw - 1)) * uint32_t(sizeof(TX));
+            auto start = [&](int64_t a, int64_t in, int C) __attribute__((always_inline)) {
+                pa = reinterpret_cast<const char *>(data + a);
+                px = reinterpret_cast<const char *>(xbase + in);
+                left = C;
+                oa = oa0;
+                ox = ox0;
+                oa_last = uint32_t((((C + W - 1) / W) - 1) * R + rr) * 16u;
+                ox_last = uint32_t(C - 1) * uint32_t(sizeof(TX));
+            };
+            auto open = [&](int kk) __attribute__((always_inline)) {   // block kk of the row, 64 descriptors at a time
+                const int j = kk & 63;
+                if (j == 0) {
+                    my = blks[rd.b0 + (kk + lane < nb ? kk + lane : nb - 1)];
+                    if constexpr (KIND == ELEM_BF16) sc = scales[my.sidx];
+                    // used here, so that the wait for these loads stays on this path
+                    asm volatile("" : "+v"(my.a), "+v"(my.in), "+v"(my.C), "+v"(sc));
+                }
+                start(readlane64(my.a, j), readlane64(my.in, j), __builtin_amdgcn_readlane(my.C, j));
+                if constexpr (KIND == ELEM_BF16)
+                    scale = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(sc), j));
+            };
+            auto load = [&](Step &st) __attribute__((always_inline)) {
+                st.left = left;
+                st.scale = scale;
+                st.a = __builtin_nontemporal_load(reinterpret_cast<const V *>(pa + min(oa, oa_last)));
+                st.x = *reinterpret_cast<const TX *>(px + min(ox, ox_last));
+                if (k < nb) {   // wave-uniform
+                    if (left > gw) {
+                        left -= gw;
+                        oa += oa_step;
+                        ox += uint32_t(gw) * uint32_t(sizeof(TX));
+                    } else if (++k < nb) {
+                        open(k);
+                    }
+                }
+            };
+            P part = P(0);
+            auto use = [&](const Step &st) __attribute__((always_inline)) {
+                const bool whole = st.left >= gw;   // wave-uniform: the step's columns all exist
+                P xv = P(st.x);
+                if (!whole) xv = lane < st.left ? xv : P(0);
+                xs[wv][lane] = xv;
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+                P v[W], x[W];
+                E::unpack(st.a, v);
+#pragma unroll
+                for (int w = 0; w < W; ++w) x[w] = xs[wv][grp * W + w];
+                if (whole || grp * W < st.left) {
+#pragma unroll
+                    for (int w = 0; w < W; ++w) part = fma(v[w], x[w], part);
+                }
+                if (st.left <= gw) {   // wave-uniform: the block's last step
+                    if constexpr (KIND == ELEM_BF16) acc += double(part) * double(st.scale);
+                    else acc += double(part);
+                    part = P(0);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+                __builtin_amdgcn_wave_barrier();
+                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+            };
+            // the first block's descriptor by itself: a scalar load returns sooner
+            start(first.a, first.in, first.C);
+            if constexpr (KIND == ELEM_BF16) scale = scales[first.sidx];
+            Step ring[D];
+#pragma unroll
+            for (int s = 0; s < D; ++s) load(ring[s]);
+            int i = 0;
+            for (; i + D <= nsteps; i += D) {
+#pragma unroll
+                for (int s = 0; s < D; ++s) {
+                    use(ring[s]);
+                    load(ring[s]);
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < D - 1; ++s)
+                if (i + s < nsteps) use(ring[s]);
+        };
+        if constexpr (std::is_same<TV, double>::value) {
+            steps(std::true_type{});   // either input is FP64
+        } else {
+            if (rd.sel & ROW_IN_X) steps(std::true_type{});
+            else steps(std::false_type{});
+        }
+    }
+    if (G > 1) {
+        red[wv][lane] = acc;
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (lane < R)
+            for (int g2 = 1; g2 < G; ++g2) acc += red[wv][g2 * R + lane];
+    }
+    if (lane < R) {
+        if (rd.sel & ROW_OUT_P)
+            out1[rd.out + lane] = TO1(acc);
+        else
+            out0[rd.out + lane] = TV(acc);
+    }
+}
+
 // One kernel name per phase of the product, so that traces and per-kernel
 // statistics separate them; all share the block-row body.
-#define H2_BLOCKROW_KERNEL(NAME, ONE_ROUND)                                                              \
+#define H2_BLOCKROW_KERNEL(NAME)                                                             \
     template <int KIND, typename TV, typename TO1>                                                      \
     __global__ __launch_bounds__(256) void NAME(                                                        \
         const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,              \
         const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales,               \
         const TV *__restrict__ in0, const double *__restrict__ in1, const TV *__restrict__ init,         \
         TV *__restrict__ out0, TO1 *__restrict__ out1) {                                                 \
-        blockrow_body<KIND, TV, TO1, ONE_ROUND>(rows, nrows, blks, data, scales, in0, in1, init, out0, out1); \
+        blockrow_body<KIND, TV, TO1>(rows, nrows, blks, data, scales, in0, in1, init, out0, out1); \
     }
-H2_BLOCKROW_KERNEL(upsweep_kernel, true)
-H2_BLOCKROW_KERNEL(stream_kernel, false)
-H2_BLOCKROW_KERNEL(downsweep_kernel, true)
-H2_BLOCKROW_KERNEL(leafexpand_kernel, true)
+H2_BLOCKROW_KERNEL(upsweep_kernel)
+H2_BLOCKROW_KERNEL(downsweep_kernel)
+H2_BLOCKROW_KERNEL(leafexpand_kernel)
 #undef H2_BLOCKROW_KERNEL
+
+// Steps in flight per wavefront (8: 84 registers at most, 5 wavefronts per SIMD;
+// 6 and 12 measured within 5 % of it over 5,000 to 2^18 points).
+constexpr int kStreamDepth = 8;
+
+template <int KIND, typename TV, typename TO1>
+__global__ __launch_bounds__(256) void stream_kernel(
+    const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,
+    const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales, const TV *__restrict__ in0,
+    const double *__restrict__ in1, const TV *__restrict__ init, TV *__restrict__ out0, TO1 *__restrict__ out1) {
+    stream_body<KIND, TV, TO1, kStreamDepth>(rows, nrows, blks, data, scales, in0, in1, out0, out1);
+}
 
 // ---------------------------------------------------------------- half storage
 // Sums of N values per lane across the N lanes that differ in the lane bits

@@ -1,0 +1,32 @@
+"""The streaming launch at the edges of its steps: ranks from 1 to 64 (lane
+groups of 64 / R rows, widths that are no multiple of a 16-byte item), leaves
+from one point up, rows of more than 64 blocks, and lists cut into pieces or
+not, in the three storages, against the oracle's exact product of the stored values."""
+import numpy as np
+import pytest
+
+from paper_1902_01829_amd import workloads as W
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# The bounds of the product tests: FP64 sums in another order, and FP32 block
+# products of at most 64 terms under FP64 sums, against the dequantized oracle.
+TOL = {0: 1e-12, 1: 1e-6, 2: 1e-6}
+
+CASES = [(3, 2, 2, 1), (200, 2, 7, 2), (900, 3, 3, 2), (2100, 2, 33, 5), (1500, 3, 31, 3), (2500, 2, 63, 7),
+         (1300, 2, 50, 8), (9000, 3, 20, 3)]
+
+
+@pytest.mark.parametrize("storage", [0, 1, 2], ids=["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("n,dim,leaf,p", CASES)
+def test_shapes(oracle_mod, n, dim, leaf, p, storage):
+    from paper_1902_01829_amd import h2mv
+    print(f"case n={n} dim={dim} leaf={leaf} p={p} storage={storage}", flush=True)
+    rng = np.random.default_rng([n, dim, leaf, p])
+    pts, x = rng.random((n, dim)), rng.standard_normal(n)
+    A = h2mv.H2Matrix(pts, dim, leaf, p, 0.9, 0.2, storage=storage)
+    ref = oracle_mod.OracleH2(pts, leaf, p, 0.9, 0.2, storage=storage).matvec(x)
+    y = A.matvec(torch.from_numpy(x).cuda()).cpu().numpy()
+    assert np.linalg.norm(y - ref) <= TOL[storage] * np.linalg.norm(ref)
+    A.close()
