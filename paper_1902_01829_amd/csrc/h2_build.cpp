@@ -550,16 +550,12 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             A.mm_host_blks.push_back(std::move(e.blks));
         }
     };
-    auto emit_one = [&](int enc, Phase ph, int kind, const void *data, const std::vector<size_t> *order) {
-        commit(enc, ph, kind, data, encode(enc, ph, order));
-    };
     auto clear = [&]() {
         L.clear();
         pool.clear();
     };
-    auto emit = [&](Phase ph, int kind, const void *data) {
-        emit_one(0, ph, kind, data, nullptr);
-        emit_one(1, ph, kind, data, nullptr);
+    auto emit = [&](Phase ph, int kind, const void *data) {   // a sweep's tile list
+        commit(1, ph, kind, data, encode(1, ph, nullptr));
         clear();
     };
     if (lowrank) {
@@ -867,17 +863,16 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
         std::vector<int64_t> near_cum{0};
         if (split) {
             // few rows: every row cut into chunks of at most `chunk` blocks, one
-            // wavefront each, writing FP64 partial sums that a second launch adds up per row
+            // wavefront each, writing FP64 partial sums that the downsweep adds up per row
             const int chunk = int(std::max<int64_t>(1, (nblk + pieces - 1) / pieces));
             std::vector<RowDesc> rows;
             std::vector<BlkDesc> blks;
-            std::vector<h2::ReduceDesc> red;
+            std::vector<h2::SumRange> tree_sums(size_t(s.nnodes), {0, 0}), near_sums(size_t(nleaves), {0, 0});
             std::vector<size_t> first_chunk;   // per row of L: its first chunk in rows
             for (const LRow &r : L) {
                 first_chunk.push_back(rows.size());
                 const int nb = int(r.nb()), nc = std::max(1, (nb + chunk - 1) / chunk);
-                red.push_back({mv_off(r.point, r.id), int32_t(rows.size()), int32_t(rows.size() + nc), r.R,
-                               r.point ? 1 : 0});
+                (r.point ? near_sums : tree_sums)[size_t(r.id)] = {int32_t(rows.size()), int32_t(rows.size() + nc)};
                 for (int c = 0; c < nc; ++c) {   // pieces of about equal length
                     RowDesc d;
                     d.out = int64_t(rows.size()) * 64;
@@ -901,25 +896,21 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             w.nrows = int64_t(rows.size());
             w.rows = A.mem.upload(rows, stream);
             w.blks = A.mem.upload(blks, stream);
-            w.red = A.mem.upload(red, stream);
-            w.nred = int64_t(red.size());
+            A.d_tree_sums = A.mem.upload(tree_sums, stream);
+            A.d_near_sums = A.mem.upload(near_sums, stream);
             w.partials_bytes = w.nrows * 64 * 8;
             w.partials = A.mem.alloc(w.partials_bytes);
             first_chunk.push_back(rows.size());
             std::vector<RowDesc> srows;
-            std::vector<h2::ReduceDesc> sred;
             for (size_t o = 0; o < order.size(); ++o) {
                 const size_t r = order[o];
                 for (size_t c = first_chunk[r]; c < first_chunk[r + 1]; ++c) {
                     srows.push_back(rows[c]);
                     if (int64_t(o) >= ncoup) near_cum.push_back(near_cum.back() + (rows[c].b1 - rows[c].b0));
                 }
-                sred.push_back(red[r]);
                 if (int64_t(o) + 1 == ncoup) w.nsrows_coupling = int64_t(srows.size());
             }
             w.srows = A.mem.upload(srows, stream);
-            w.sred = A.mem.upload(sred, stream);
-            w.nsred_coupling = ncoup;
             w.near_cum = std::move(near_cum);
             A.lists.push_back(w);
         } else {
@@ -957,6 +948,40 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
     for (int64_t j = 0; j < nleaves; ++j) {
         lb[j] = s.begin[lf + j];
         le[j] = s.end[lf + j];
+    }
+    A.d_off_U = A.mem.upload(A.off_U, stream);
+    A.d_off_VT = A.mem.upload(A.off_VT, stream);
+    A.d_off_E = A.mem.upload(A.off_E, stream);
+    A.d_off_FT = A.mem.upload(A.off_FT, stream);
+    // the sweeps' launches
+    A.up_steps.clear();
+    A.down_steps.clear();
+    if (lowrank) {
+        // Levels per launch: as many as keep a subtree's blocks, all read by one
+        // workgroup, within 256 KiB, at least one; a launch of one level takes
+        // about 5 us, a further level in it 2 us for small blocks.  (16,384
+        // points of rank 64, FP64, 1 / 2 / 3 levels: 124 / 126 / 122 us per
+        // product; 2^18 points, FP64, 1 / 3: 1696 / 1753 us.)
+        const int64_t per_node = (mmax * k + 2 * int64_t(k) * k) * vb;
+        const int64_t budget = 256 << 10;
+        int depth = 1;
+        while (depth < h2::SWEEP_MAX_DEPTH && (per_node << (depth + 1)) <= budget) ++depth;
+        // Wavefronts per bottom node (FP64; FP32 sums of a block stay whole): enough that a lane's items of the largest
+        // block (16 bytes each) are at most 8, one round of loads (16,384 points
+        // of rank 64, FP64, 1 / 2 / 4 wavefronts: 214 / 154 / 124 us; rank 16, 4
+        // items, 1 / 2: 30 / 35 us).
+        const int cols = int(std::max<int64_t>(k, mmax)), W = 16 / h2::elem_bytes(bk);
+        const int items = ((cols + W - 1) / W + 64 / cols - 1) / (64 / cols);
+        const int levels = q - s.lmin, steps = std::max(1, (levels + depth - 1) / depth);
+        for (int i = 0; i < steps; ++i) {   // from the leaves up
+            const int top = q - int(int64_t(levels) * (i + 1) / steps), bottom = q - int(int64_t(levels) * i / steps);
+            int split = 0;
+            while (A.vec_f64 && bottom - top + split < h2::SWEEP_MAX_DEPTH && (items >> split) > 8) ++split;
+            A.up_steps.push_back({top, bottom - top, split, i == 0});
+        }
+        A.down_steps.assign(A.up_steps.rbegin(), A.up_steps.rend());
+    } else {
+        A.down_steps.push_back({q, 0, 0, true});   // y = y_near
     }
     A.d_leaf_begin = A.mem.upload(lb, stream);
     A.d_leaf_end = A.mem.upload(le, stream);

@@ -85,9 +85,9 @@ hipError_t launch_transpose_blocks(int kind, const void *src, void *dst, const T
 hipError_t launch_fill_blocks(const Geometry &g, int block_kind, void *blocks, float *scales,
                               const FillDesc *desc, int64_t nblocks, hipStream_t st);
 
-// Block-row product over one work list.  kind: element kind of data; vec_f64:
-// vector workspace (in0, init, out0) is double (else float); out1 is double in
-// the leaf phase (the result y) and of the workspace type otherwise.
+// Streaming launch over one work list.  kind: element kind of data; vec_f64:
+// vector workspace (in0, out0) is double (else float); out1 is double with
+// out1_f64 (a cut list writes FP64 partial sums), else of the workspace type.
 struct RowLaunch {
     const RowDesc *rows;
     int64_t nrows;
@@ -96,30 +96,50 @@ struct RowLaunch {
     const float *scales;
     const void *in0;        // tree vectors
     const double *in1;      // point vector x
-    const void *init;
     void *out0;
     void *out1;
     int lds_bytes = 0;      // LDS requested beyond the kernel's own (caps workgroups per compute unit)
 };
-// Phases of the product (each launches its own kernel name).
+// Phases of the product (the tile launches have a kernel name each).
 enum { PHASE_UP = 0, PHASE_STREAM = 1, PHASE_DOWN = 2, PHASE_LEAF = 3 };
-// out1_f64: -1 = by phase (the leaf phase writes the FP64 result), 0/1 forced
-// (a split stream list writes FP64 partial sums).
-hipError_t launch_blockrow(const RowLaunch &L, int kind, bool vec_f64, int phase, hipStream_t st, int out1_f64 = -1);
+hipError_t launch_stream(const RowLaunch &L, int kind, bool vec_f64, bool out1_f64, hipStream_t st);
 
-// A block row of a small matrix's single-vector stream list, cut into chunks
-// of a few blocks: the chunks' partial sums (FP64, 64 per chunk) are added in
-// chunk order into the row's output segment.
+// Levels `level` .. `level` + `depth` of a tree sweep in one launch, a
+// workgroup of 2^(depth + split) wavefronts per node of `level`.
+constexpr int SWEEP_MAX_DEPTH = 4;   // largest depth + split (1024 threads)
+struct SumRange {
+    int32_t c0, c1;   // chunks [c0, c1) of a cut stream list
+};
+struct SweepLaunch {
+    const void *basis;
+    const int64_t *off_leaf;         // V_j^T (up) or U_j (down; NULL: no basis) per leaf, element offsets
+    const int64_t *off_tr;           // F_c^T (up) or E_c (down) per node
+    const int64_t *leaf_begin, *leaf_end;
+    const double *x;                 // up, leaf
+    double *y;                       // down, leaf
+    void *tree;                      // x^ (up) or y^ (down)
+    const void *near;                // down, leaf: y_near
+    const double *partials;          // down: chunk sums of a cut stream list, else NULL
+    const SumRange *tree_sums, *near_sums;   // per node, per leaf
+    int stride;                      // elements per node in tree
+    int level, depth, split;
+    bool leaf;                       // level + depth is the leaf level: leaf projection / leaf expansion too
+    bool root_done;                  // down: the y^ of the nodes of `level` is complete
+    int rank[SWEEP_MAX_DEPTH + 1];   // ranks of the levels
+};
+hipError_t launch_sweep(const SweepLaunch &L, bool up, bool vec_f64, hipStream_t st);
+
+// Row sums of a list stored by halves: a segment's partial slots (64 values
+// each), added in order to its output segment.
 struct ReduceDesc {
     int64_t out;      // element offset of the output segment
-    int32_t c0, c1;   // its chunks
+    int32_t c0, c1;   // its slots
     int32_t R;        // rows of the segment
     int32_t point;    // 1: the near-field point vector (out1), 0: the tree vector (out0)
 };
-// partials: FP64, or FP32 with partials_f32; add: the sums start from the
-// segments' current values.
-hipError_t launch_reduce_chunks(const ReduceDesc *desc, int64_t n, const void *partials, bool partials_f32, void *out0,
-                                void *out1, bool vec_f64, hipStream_t st, bool add = false);
+// partials: of the vectors' type.
+hipError_t launch_reduce_chunks(const ReduceDesc *desc, int64_t n, const void *partials, void *out0, void *out1,
+                                bool vec_f64, hipStream_t st);
 // Stream phase of a matrix stored by halves (blocks with j >= i): rows write
 // their direct sums to out0/out1 (the input segment of a row has its output
 // segment's offset); slot[b] >= 0 names the 64-double partial slot that

@@ -105,29 +105,32 @@ struct WorkList {
     int64_t nitems = 0;
     const int32_t *pitems = nullptr;  // tile lists: pair items (two per workgroup) in dispatch order
     int64_t npitems = 0;
-    // split stream list (single vector, small matrices): the rows are chunks
-    // writing FP64 partial sums, added up by a second launch
-    const h2::ReduceDesc *red = nullptr;
-    int64_t nred = 0;
+    // cut stream list (single vector): the rows are chunks writing FP64 partial
+    // sums, which the downsweep adds up (tree_sums, near_sums)
     void *partials = nullptr;   // FP64 (FP32 for the half-storage list of a reduced-storage matrix)
     int64_t partials_bytes = 0;
     // stream list of a matrix stored by halves: the wavefronts' row groups,
     // every block's slot code and the groups' merged partial slots (see
     // h2::HalfGroup); red then adds the slots to the row sums
+    const h2::ReduceDesc *red = nullptr;
+    int64_t nred = 0;
     const int32_t *slot = nullptr;
     const h2::HalfGroup *groups = nullptr;
     int64_t ngroups = 0;
     const int32_t *gslot = nullptr;
     // single-vector stream list, full storage: the same rows (chunks, for a
-    // split list) with the coupling rows first and the near-field rows after,
-    // each part in the list's own order, and (split list) the row sums
-    // ordered the same way -- the near field can then run as a launch of its
-    // own (H2_SCHEDULE_STREAMED)
+    // cut list) with the coupling rows first and the near-field rows after,
+    // each part in the list's own order -- the near field can then run as a
+    // launch of its own (H2_SCHEDULE_STREAMED)
     const h2::RowDesc *srows = nullptr;
     int64_t nsrows_coupling = 0;
-    const h2::ReduceDesc *sred = nullptr;
-    int64_t nsred_coupling = 0;
     std::vector<int64_t> near_cum;   // blocks of the near-field rows of srows, cumulative (size rows + 1)
+};
+
+// One launch of a tree sweep of the single-vector product (h2::SweepLaunch).
+struct SweepStep {
+    int level, depth, split;
+    bool leaf;
 };
 
 // A single-vector stream list with fewer than two thirds as many block rows as
@@ -174,7 +177,10 @@ struct h2_matrix_ {
     void *basis = nullptr, *blocks = nullptr;
     float *scales = nullptr;
     void *xh = nullptr, *yh = nullptr, *ynear = nullptr;
-    std::vector<h2i::WorkList> lists;      // single right-hand side (vector offsets)
+    std::vector<h2i::WorkList> lists;      // single right-hand side: the streaming list (vector offsets)
+    std::vector<h2i::SweepStep> up_steps, down_steps;   // single right-hand side: the sweeps, in launch order
+    int64_t *d_off_U = nullptr, *d_off_VT = nullptr, *d_off_E = nullptr, *d_off_FT = nullptr;   // off_* on the device
+    h2::SumRange *d_tree_sums = nullptr, *d_near_sums = nullptr;   // cut streaming list: chunks per node / leaf
     std::vector<h2i::WorkList> mm_lists;   // tiles of MM_TILE right-hand sides (tile offsets)
     std::vector<std::vector<h2::RowDesc>> mm_host_rows;   // host copies of mm_lists (for batches)
     std::vector<std::vector<h2::BlkDesc>> mm_host_blks;

@@ -1,8 +1,8 @@
 // HIP kernels of libh2mv for gfx950 (MI355X): generation of the H^2
-// representation on the device, and the block-row streaming kernel that runs
-// every phase of the product (Sec. 4): leaf projection and upsweep (Sec. 4.2),
-// tree multiplication with all levels in one launch together with the dense
-// near field (Sec. 4.3, Sec. 4.1), downsweep and leaf expansion (Sec. 4.4).
+// representation on the device, and the phases of the single-vector product
+// (Sec. 4): leaf projection and upsweep (Sec. 4.2), tree multiplication with
+// all levels in one launch together with the dense near field (Sec. 4.3,
+// Sec. 4.1), downsweep and leaf expansion (Sec. 4.4).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -253,13 +253,12 @@ __global__ __launch_bounds__(256) void fill_blocks_bf16_kernel(Geometry g, uint1
     if (threadIdx.x == 0) scales[d.sidx] = s;
 }
 
-// ---------------------------------------------------------------- chunk sums
-// One wavefront per segment: lane r adds partials[c * 64 + r] (FP64 or FP32)
-// over the segment's chunks in order, in FP64, and stores the segment's
-// element r; with ADD the sum starts from the element's current value.
-template <typename TV, typename TP, bool ADD>
+// ---------------------------------------------------------------- slot sums
+// One wavefront per segment: lane r adds partials[c * 64 + r] over the
+// segment's slots in order, in FP64, to the segment's element r.
+template <typename TV>
 __global__ __launch_bounds__(256) void reduce_chunks_kernel(const ReduceDesc *__restrict__ desc, int64_t n,
-                                                            const TP *__restrict__ partials, TV *__restrict__ out0,
+                                                            const TV *__restrict__ partials, TV *__restrict__ out0,
                                                             TV *__restrict__ out1) {
     const int64_t i = int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r = threadIdx.x & 63;
@@ -267,7 +266,7 @@ __global__ __launch_bounds__(256) void reduce_chunks_kernel(const ReduceDesc *__
     const ReduceDesc d = desc[i];
     if (r >= d.R) return;
     TV *dst = (d.point ? out1 : out0) + d.out + r;
-    double acc = ADD ? double(*dst) : 0.0;
+    double acc = double(*dst);
     int c = d.c0;
     for (; c + 8 <= d.c1; c += 8) {   // eight loads in flight, added in order
         double v[8];
@@ -303,140 +302,301 @@ __global__ __launch_bounds__(256) void transpose_blocks_kernel(const T *__restri
     }
 }
 
-// ---------------------------------------------------------------- block-row product
-// Tree sweeps and leaf launch: one wavefront per output segment, whose row
-// holds one or two blocks.  The block's input segment (<= 64 values) is staged
-// in the wave's LDS slot; each lane streams its row's 16-byte items of the
-// block with non-temporal loads and accumulates the block's dot products.  One
-// block's partial sum is kept in the block arithmetic type, sums over blocks
-// in FP64.  All of a lane's items of a block of at most 8 per lane are requested
-// at once, before the input segment, so the block costs one memory round trip
-// instead of one per eight items; on the few rows of the levels near the root
-// that chain is the launch's whole duration.
-template <int KIND, typename TV, typename TO1>
-__device__ __forceinline__ void blockrow_body(
-    const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,
-    const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales,
-    const TV *__restrict__ in0, const double *__restrict__ in1, const TV *__restrict__ init,
-    TV *__restrict__ out0, TO1 *__restrict__ out1) {
+// ---------------------------------------------------------------- tree sweeps
+// A launch takes up to SWEEP_MAX_DEPTH levels of the tree: one workgroup per
+// subtree of 2^depth bottom nodes, 2^depth 2^split wavefronts, the subtree's
+// vectors in LDS.  Every level is then that many equal pieces of work -- 2^p
+// nodes at depth p, their blocks' columns split over the wavefronts -- and
+// costs one exchange through LDS instead of a launch and its chain of memory
+// round trips: a piece's items (at most 8 per lane by the choice of split) are
+// requested before the level above is summed, behind barriers that order LDS
+// only.  Partial sums are added in a fixed order; FP32 bases keep a block's FP32
+// sum whole (pieces are blocks, split = 0), as splitting it would round it
+// differently.  Bound by latency for small
+// matrices -- the code is kept short, with one copy of each step, as its first
+// fetch is part of it -- and by the blocks' bytes near the leaves of large ones.
+// Against one launch per level, a launch for the leaves and one for the chunk
+// sums: 4,096 points of rank 16 FP64 41 -> 31 us (12 -> 3 launches), 16,384
+// points of rank 64 FP64 153 -> 122 us, FP32 98 -> 81, BF16 80 -> 63 us; 60,000
+// points of rank 49 FP32 262 -> 205 us; 2^20 points of rank 64 6.93 -> 6.85 ms.
+
+// Barrier of a workgroup that exchanges data through LDS alone: unlike
+// __syncthreads, it does not wait for the global loads in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// One wavefront's piece of a block: lane = grp * R + r takes the column groups
+// c0 + grp, c0 + grp + G, ... below c1 of row r (G = 64 / R lane groups); the
+// first N are requested ahead of their use.
+template <int KIND>
+struct Piece {
     using E = Elem<KIND>;
+    using V = typename E::V;
     using P = typename E::P;
-    constexpr int W = E::W;
-    __shared__ __attribute__((aligned(16))) P xs[4][64];
-    __shared__ double red[4][64];
-    // the wave index made uniform, so that the row and block descriptors come
-    // through scalar loads and a block's base address is uniform (its loads
-    // then take 32-bit lane offsets)
-    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int64_t row = int64_t(blockIdx.x) * 4 + wv;
-    if (row >= nrows) return;
-    const RowDesc rd = rows[row];
-    const int R = rd.R, G = 64 / R, grp = lane / R, rr = lane - grp * R;
-    const bool in_x = (rd.sel & ROW_IN_X) != 0;
-    double acc = 0.0;
-    for (int b = rd.b0; b < rd.b1; ++b) {
-        const BlkDesc bd = blks[b];
-        const int C = bd.C, CW = (C + W - 1) / W;
-        using V = typename E::V;
-        P part = P(0);
-        bool done = false;
-        {
-            // Blocks of at most 8 items per lane: N items, a compile-time
-            // count (the smallest of 2, 4, 8 covering the block's ceil(CW / G)
-            // column groups per lane, a wave-uniform choice), so that they
-            // stay in registers.  Item t is column group grp + t G, clamped
-            // into the block (every load is valid; the clamped ones are not
-            // used).  Larger blocks take the streaming loop below (a fully
-            // unrolled round of 16 or 32 items made the kernel's code several
-            // times longer and the launches near the root slower).
-            auto round = [&](auto n) {
-                constexpr int N = decltype(n)::value;
-                V raw[N];
-                // a wave-uniform base and 32-bit lane offsets (a block is at
-                // most 32 KiB), so the loads need no 64-bit address per item
-                const char *base = reinterpret_cast<const char *>(data + bd.a);
+    static constexpr int W = E::W;
+    static constexpr int N = KIND == ELEM_F64 ? 8 : 16;
+    const char *base;
+    uint32_t row;            // the lane's byte offset of column group 0
+    int R, G, first, c1, cw_last, n;   // n: items per lane, wave-uniform
+    bool live;
+    V raw[N];
+
+    // part k of ks of the R x C block at base
+    __device__ __forceinline__ void request(const typename E::T *block, int rows, int C, int k, int ks, int lane) {
+        base = reinterpret_cast<const char *>(block);
+        R = rows;
+        G = 64 / R;
+        const int grp = lane / R, CW = (C + W - 1) / W, c0 = CW * k / ks;
+        live = grp < G;
+        row = uint32_t(lane - grp * R) * 16u;
+        first = c0 + (live ? grp : 0);
+        c1 = CW * (k + 1) / ks;
+        cw_last = CW - 1;
+        n = (c1 - c0 + G - 1) / G;
+        // (four at a time; the addresses past the piece are clamped into the block)
 #pragma unroll
-                for (int t = 0; t < N; ++t) {
-                    const int cw = grp + t * G;
-                    const uint32_t off = uint32_t((cw < CW ? cw : CW - 1) * R + rr) * 16u;
-                    raw[t] = __builtin_nontemporal_load(reinterpret_cast<const V *>(base + off));
-                }
-                P xv = P(0);
-                if (lane < C) xv = in_x ? P(in1[bd.in + lane]) : P(in0[bd.in + lane]);
-                xs[wv][lane] = xv;
-                __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-                __builtin_amdgcn_wave_barrier();
-                __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-                P s = P(0);
-                if (grp < G) {
+        for (int u = 0; u < N; u += 4) {
+            if (u >= n) continue;   // wave-uniform
 #pragma unroll
-                    for (int t = 0; t < N; ++t) {
-                        const int cw = grp + t * G;
-                        if (cw < CW) {
-                            P v[W];
-                            E::unpack(raw[t], v);
-#pragma unroll
-                            for (int w = 0; w < W; ++w) s = fma(v[w], xs[wv][cw * W + w], s);
-                        }
-                    }
-                }
-                return s;
-            };
-            const int ni = (CW + G - 1) / G;
-            using std::integral_constant;
-            done = ni <= 8;
-            if (ni <= 0)
-                ;   // a block without columns adds nothing
-            else if (ni <= 2)
-                part = round(integral_constant<int, 2>{});
-            else if (ni <= 4)
-                part = round(integral_constant<int, 4>{});
-            else if (ni <= 8)
-                part = round(integral_constant<int, 8>{});
+            for (int t = u; t < u + 4; ++t) raw[t] = item(first + t * G);
         }
-        if (!done) {
-            P xv = P(0);
-            if (lane < C) xv = in_x ? P(in1[bd.in + lane]) : P(in0[bd.in + lane]);
-            xs[wv][lane] = xv;
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-            if (grp < G) {
-                const V *p = reinterpret_cast<const V *>(data + bd.a) + (grp * R + rr);
-                const int stride = G * R;
-#pragma unroll 8
-                for (int cw = grp; cw < CW; cw += G, p += stride) {
-                    const V raw = __builtin_nontemporal_load(p);
-                    P v[W];
-                    E::unpack(raw, v);
+    }
+    __device__ __forceinline__ V item(int cw) const {
+        return __builtin_nontemporal_load(
+            reinterpret_cast<const V *>(base + (__umul24(cw < cw_last ? cw : cw_last, R) * 16u + row)));
+    }
+    // its products with the input x (LDS, zero past the block's columns)
+    __device__ __forceinline__ double products(const P *x) const {
+        P s = P(0);
+        // four items: the inputs read together, items past the piece left out
+        auto add = [&](const V *r, int cw0) __attribute__((always_inline)) {
+            P xi[4][W];
 #pragma unroll
-                    for (int w = 0; w < W; ++w) part = fma(v[w], xs[wv][cw * W + w], part);
-                }
+            for (int t = 0; t < 4; ++t) {
+                const int cw = cw0 + t * G, cl = cw < cw_last ? cw : cw_last;
+#pragma unroll
+                for (int w = 0; w < W; ++w) xi[t][w] = x[cl * W + w];
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                P v[W], q = s;
+                E::unpack(r[t], v);
+#pragma unroll
+                for (int w = 0; w < W; ++w) q = fma(v[w], xi[t][w], q);
+                s = cw0 + t * G < c1 ? q : s;
+            }
+        };
+#pragma unroll
+        for (int u = 0; u < N; u += 4)
+            if (u < n) add(raw + u, first + u * G);
+#pragma unroll 1
+        for (int u = N; u < n; u += 4) {
+            V r[4];
+#pragma unroll
+            for (int t = 0; t < 4; ++t) r[t] = item(first + (u + t) * G);
+            add(r, first + u * G);
+        }
+        return double(s);
+    }
+};
+
+// The np pieces of one node are stored one after the other, G R values each
+// (64 reserved).  Row r: lane group by lane group the sum of the pieces' values
+// for FP32 bases (at most two pieces, whole blocks), piece by piece for FP64;
+// added in order, the loads of eight values at a time.
+template <int KIND>
+__device__ __forceinline__ double add_pieces(const double *part, int np, int R, int r) {
+    const int G = 64 / R, n = np * G;
+    double t = 0.0;
+    if constexpr (KIND == ELEM_F64) {
+#pragma unroll 1
+        for (int c = 0; c < n; c += 8) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(c + u < n ? c + u : c) * R + r];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) t += c + u < n ? v[u] : 0.0;
+        }
+    } else {
+#pragma unroll 1
+        for (int g = 0; g < G; g += 4) {
+            double v[2][4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int c = g + u < G ? g + u : g;
+                v[0][u] = part[c * R + r];
+                v[1][u] = np > 1 ? part[(G + c) * R + r] : 0.0;
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) t += g + u < G ? v[0][u] + v[1][u] : 0.0;
+        }
+    }
+    return t;
+}
+
+// log2 of the wavefronts that share the 2^d blocks of a level, 2^ws in all.
+template <int KIND>
+__device__ __forceinline__ int sharing(int ws, int d) { return KIND == ELEM_F64 ? ws : d; }
+
+// Leaf projection x^_j = V_j^T x(j) (with a.leaf) and
+// x^_p = F_c1^T x^_c1 + F_c2^T x^_c2 for the depths above the bottom one.
+template <int KIND>
+__global__ __launch_bounds__(1024) void upsweep_kernel(const SweepLaunch a, const int64_t *__restrict__ off_leaf,
+                                                       const int64_t *__restrict__ off_tr,
+                                                       const int64_t *__restrict__ leaf_begin,
+                                                       const int64_t *__restrict__ leaf_end) {
+    using P = typename Elem<KIND>::P;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int T = a.depth, S = a.split, WS = T + S, NB = 1 << T;   // NB bottom nodes
+    double *part = reinterpret_cast<double *>(lds);                // (1 << WS) x 64
+    P *xs = reinterpret_cast<P *>(part + (64 << WS));              // leaf inputs: NB x 64
+    P *xv = xs + (a.leaf ? NB * 64 : 0);                           // the subtree's x^, heap order: (2 NB - 1) x 64
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t b = blockIdx.x;
+    const auto *basis = static_cast<const typename Elem<KIND>::T *>(a.basis);
+    P *tree = static_cast<P *>(a.tree);
+    auto node = [&](int p, int i) { return (int64_t(1) << (a.level + p)) - 1 + (b << p) + i; };
+    // depths a.leaf ? T : T - 1 down to 0, this wavefront's piece of each: of the
+    // leaf basis (depth T) or of a child's transfer
+    Piece<KIND> piece;
+    if (!a.leaf) {
+        if (wv < NB) xv[(NB - 1 + wv) * 64 + lane] = lane < a.rank[T] ? tree[node(T, wv) * a.stride + lane] : P(0);
+    } else if (wv < NB) {
+        const int64_t j = (b << T) + wv, x0 = leaf_begin[j];
+        xs[wv * 64 + lane] = lane < int(leaf_end[j] - x0) ? P(a.x[x0 + lane]) : P(0);
+    }
+    const P *in = nullptr;   // the piece's input
+    bool active = false;     // whether this wavefront has a piece
+#pragma unroll 1
+    for (int p = a.leaf ? T : T - 1, have = 0; p >= -1; --p, have = 1) {
+        if (have) {
+            lds_barrier();
+            // piece `sub` of its node of depth p + 1, whose blocks are those of depth p + 1 (leaf) or p + 2
+            const int sub = wv & ((1 << (sharing<KIND>(WS, p + 1 == T ? T : p + 2) - p - 1)) - 1);
+            const double v = active ? piece.products(in) : 0.0;
+            if (active && piece.live) part[(wv - sub) * 64 + sub * piece.G * piece.R + lane] = v;
+        }
+        const int shared = have ? sharing<KIND>(WS, p + 1 == T ? T : p + 2) : 0;
+        if (p >= 0) {
+            const bool at_leaf = p == T;
+            const int d = at_leaf ? T : p + 1, w = sharing<KIND>(WS, d), ks = 1 << (w - d), i = wv >> (w - d);   // input node i of depth d
+            active = wv < (1 << w);   // wave-uniform
+            if (active) {
+                const int64_t j = (b << T) + i;
+                const int64_t off = at_leaf ? off_leaf[j] : off_tr[node(d, i)];
+                const int C = at_leaf ? int(leaf_end[j] - leaf_begin[j]) : a.rank[d];
+                in = at_leaf ? xs + i * 64 : xv + ((1 << d) - 1 + i) * 64;
+                piece.request(basis + off, a.rank[p], C, wv & (ks - 1), ks, lane);
             }
         }
-        if constexpr (KIND == ELEM_BF16)
-            acc += double(part) * double(scales[bd.sidx]);
-        else
-            acc += double(part);
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        if (have) {   // sums of depth p + 1: wavefront i adds node i's pieces, in order
+            lds_barrier();
+            const int d = p + 1;
+            if (wv < (1 << d)) {
+                const int R = a.rank[d], nw = 1 << (shared - d);
+                const P v = lane < R ? P(add_pieces<KIND>(part + wv * nw * 64, nw, R, lane)) : P(0);
+                xv[((1 << d) - 1 + wv) * 64 + lane] = v;
+                if (lane < R) tree[node(d, wv) * a.stride + lane] = v;
+            }
+        }
     }
-    if (G > 1) {
-        red[wv][lane] = acc;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-        if (lane < R)
-            for (int g2 = 1; g2 < G; ++g2) acc += red[wv][g2 * R + lane];
+}
+
+// y^_c = (its tree multiplication's sum) + E_c y^_parent for the depths below
+// the root, and with a.leaf y(j) = y_near(j) + U_j y^_j (FP64).  The sums come
+// from the stream launch's chunks where its list was cut (a.partials), in
+// order, else from the tree and the near-field vector.
+template <int KIND>
+__global__ __launch_bounds__(1024) void downsweep_kernel(const SweepLaunch a, const int64_t *__restrict__ off_leaf,
+                                                         const int64_t *__restrict__ off_tr,
+                                                         const int64_t *__restrict__ leaf_begin,
+                                                         const int64_t *__restrict__ leaf_end,
+                                                         const SumRange *__restrict__ tree_sums,
+                                                         const SumRange *__restrict__ near_sums) {
+    using P = typename Elem<KIND>::P;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int T = a.depth, S = a.split, WS = T + S, NB = 1 << T;
+    double *part = reinterpret_cast<double *>(lds);          // (1 << WS) x 64
+    double *iv = part + (64 << WS);          // sums of the subtree's nodes, heap order, then near fields: (3 NB - 1) x 64
+    P *yv = reinterpret_cast<P *>(iv + (3 * NB - 1) * 64);   // its y^: (2 NB - 1) x 64
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int64_t b = blockIdx.x;
+    const auto *basis = static_cast<const typename Elem<KIND>::T *>(a.basis);
+    P *tree = static_cast<P *>(a.tree);
+    auto node = [&](int p, int i) { return (int64_t(1) << (a.level + p)) - 1 + (b << p) + i; };
+    const bool lowrank = !a.leaf || off_leaf != nullptr;
+    const int last = !lowrank ? 0 : a.leaf ? T + 1 : T;   // depths 1 .. T: transfers, T + 1: the leaf basis
+    Piece<KIND> piece;
+    const P *in = nullptr;   // the piece's input
+    bool active = false;     // whether this wavefront has a piece
+#pragma unroll 1
+    for (int p = 1, have = 0; p <= last + 1; ++p, have = 1) {
+        if (have) {
+            lds_barrier();
+            const int d = p - 1 <= T ? p - 1 : T, sub = wv & ((1 << (sharing<KIND>(WS, d) - d)) - 1);   // piece `sub` of its node
+            const double v = active ? piece.products(in) : 0.0;
+            if (active && piece.live) part[(wv - sub) * 64 + sub * piece.G * piece.R + lane] = v;
+        }
+        if (p <= last) {
+            const bool at_leaf = p > T;
+            const int d = at_leaf ? T : p, w = sharing<KIND>(WS, d), ks = 1 << (w - d), i = wv >> (w - d);   // output node i of depth d
+            active = wv < (1 << w);   // wave-uniform
+            if (active) {
+                const int64_t j = (b << T) + i;
+                const int64_t off = at_leaf ? off_leaf[j] : off_tr[node(d, i)];
+                const int R = at_leaf ? int(leaf_end[j] - leaf_begin[j]) : a.rank[d];
+                in = yv + (at_leaf ? (1 << T) - 1 + i : (1 << (d - 1)) - 1 + (i >> 1)) * 64;
+                piece.request(basis + off, R, a.rank[p - 1], wv & (ks - 1), ks, lane);
+            }
+        }
+        if (!have) {   // the starting sums of the subtree's nodes and of its leaves' near fields
+#pragma unroll 1
+            for (int h = lowrank ? wv : 2 * NB - 1 + wv; h < (a.leaf ? 3 : 2) * NB - 1; h += 1 << WS) {
+                const bool leaf = h >= 2 * NB - 1;
+                const int d = leaf ? T : 31 - __builtin_clz(unsigned(h + 1)), i = leaf ? h - (2 * NB - 1) : h + 1 - (1 << d);
+                const int64_t v = leaf ? (b << T) + i : node(d, i);
+                const int64_t y0 = leaf ? leaf_begin[v] : v * a.stride;
+                const int n = leaf ? int(leaf_end[v] - y0) : a.rank[d];
+                double t = 0.0;
+                if (!a.partials || (h == 0 && a.root_done)) {
+                    if (lane < n) t = double((leaf ? static_cast<const P *>(a.near) : tree)[y0 + lane]);
+                } else {
+                    const SumRange r = (leaf ? near_sums : tree_sums)[v];
+#pragma unroll 1
+                    for (int c = r.c0; c < r.c1; c += 8) {   // eight loads in flight, added in order
+                        double w[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            w[u] = a.partials[int64_t(c + u < r.c1 ? c + u : c) * 64 + (lane < n ? lane : 0)];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u) t += c + u < r.c1 ? w[u] : 0.0;
+                    }
+                    if (lane >= n) t = 0.0;
+                }
+                // (rounded to the vectors' type, as the stream launch stores a sum that is not cut)
+                if (h > 0 || leaf) iv[h * 64 + lane] = double(P(t));
+                else yv[lane] = P(t);
+            }
+            if (last == 0) lds_barrier();
+        } else {       // sums of depth p - 1: wavefront i adds node i's pieces, in order
+            lds_barrier();
+            const int d = p - 1;
+            if (d <= T && wv < (1 << d)) {
+                const int R = a.rank[d], nw = 1 << (sharing<KIND>(WS, d) - d), h = (1 << d) - 1 + wv;
+                const P v = lane < R ? P(iv[h * 64 + lane] + add_pieces<KIND>(part + wv * nw * 64, nw, R, lane)) : P(0);
+                yv[h * 64 + lane] = v;
+                if (d == T && !a.leaf && lane < R) tree[node(d, wv) * a.stride + lane] = v;
+            }
+        }
     }
-    if (lane < R) {
-        const double res = rd.init >= 0 ? double(init[rd.init + lane]) + acc : acc;
-        if (rd.sel & ROW_OUT_P)
-            out1[rd.out + lane] = TO1(res);
-        else
-            out0[rd.out + lane] = TV(res);
+    if (a.leaf && wv < NB) {
+        const int64_t j = (b << T) + wv, y0 = leaf_begin[j];
+        const int m = int(leaf_end[j] - y0);
+        if (lane < m)
+            a.y[y0 + lane] = iv[(2 * NB - 1 + wv) * 64 + lane] + (lowrank ? add_pieces<KIND>(part + (wv << (sharing<KIND>(WS, T) - T)) * 64, 1 << (sharing<KIND>(WS, T) - T), m, lane) : 0.0);
     }
 }
 
@@ -616,22 +776,6 @@ __device__ __forceinline__ void stream_body(
     }
 }
 
-// One kernel name per phase of the product, so that traces and per-kernel
-// statistics separate them; all share the block-row body.
-#define H2_BLOCKROW_KERNEL(NAME)                                                             \
-    template <int KIND, typename TV, typename TO1>                                                      \
-    __global__ __launch_bounds__(256) void NAME(                                                        \
-        const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,              \
-        const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales,               \
-        const TV *__restrict__ in0, const double *__restrict__ in1, const TV *__restrict__ init,         \
-        TV *__restrict__ out0, TO1 *__restrict__ out1) {                                                 \
-        blockrow_body<KIND, TV, TO1>(rows, nrows, blks, data, scales, in0, in1, init, out0, out1); \
-    }
-H2_BLOCKROW_KERNEL(upsweep_kernel)
-H2_BLOCKROW_KERNEL(downsweep_kernel)
-H2_BLOCKROW_KERNEL(leafexpand_kernel)
-#undef H2_BLOCKROW_KERNEL
-
 // Steps in flight per wavefront (8: 84 registers at most, 5 wavefronts per SIMD;
 // 6 and 12 measured within 5 % of it over 5,000 to 2^18 points).
 constexpr int kStreamDepth = 8;
@@ -640,7 +784,7 @@ template <int KIND, typename TV, typename TO1>
 __global__ __launch_bounds__(256) void stream_kernel(
     const RowDesc *__restrict__ rows, int64_t nrows, const BlkDesc *__restrict__ blks,
     const typename Elem<KIND>::T *__restrict__ data, const float *__restrict__ scales, const TV *__restrict__ in0,
-    const double *__restrict__ in1, const TV *__restrict__ init, TV *__restrict__ out0, TO1 *__restrict__ out1) {
+    const double *__restrict__ in1, TV *__restrict__ out0, TO1 *__restrict__ out1) {
     stream_body<KIND, TV, TO1, kStreamDepth>(rows, nrows, blks, data, scales, in0, in1, out0, out1);
 }
 
@@ -814,32 +958,12 @@ __global__ __launch_bounds__(256) void stream_half_kernel(
 constexpr int kRowsPerBlock = 4;
 
 template <int KIND, typename TV, typename TO1>
-hipError_t run_blockrow(const RowLaunch &L, int phase, hipStream_t st) {
+hipError_t run_stream(const RowLaunch &L, hipStream_t st) {
     if (L.nrows <= 0) return hipSuccess;
     const dim3 grid(unsigned((L.nrows + kRowsPerBlock - 1) / kRowsPerBlock)), block(256);
-    const auto *data = static_cast<const typename Elem<KIND>::T *>(L.data);
-    const auto *in0 = static_cast<const TV *>(L.in0);
-    const auto *init = static_cast<const TV *>(L.init);
-    auto *out0 = static_cast<TV *>(L.out0);
-    auto *out1 = static_cast<TO1 *>(L.out1);
-    switch (phase) {
-        case PHASE_UP:
-            hipLaunchKernelGGL((upsweep_kernel<KIND, TV, TO1>), grid, block, L.lds_bytes, st, L.rows, L.nrows, L.blks, data,
-                               L.scales, in0, L.in1, init, out0, out1);
-            break;
-        case PHASE_STREAM:
-            hipLaunchKernelGGL((stream_kernel<KIND, TV, TO1>), grid, block, L.lds_bytes, st, L.rows, L.nrows, L.blks, data,
-                               L.scales, in0, L.in1, init, out0, out1);
-            break;
-        case PHASE_DOWN:
-            hipLaunchKernelGGL((downsweep_kernel<KIND, TV, TO1>), grid, block, L.lds_bytes, st, L.rows, L.nrows, L.blks,
-                               data, L.scales, in0, L.in1, init, out0, out1);
-            break;
-        default:
-            hipLaunchKernelGGL((leafexpand_kernel<KIND, TV, TO1>), grid, block, L.lds_bytes, st, L.rows, L.nrows, L.blks,
-                               data, L.scales, in0, L.in1, init, out0, out1);
-            break;
-    }
+    hipLaunchKernelGGL((stream_kernel<KIND, TV, TO1>), grid, block, L.lds_bytes, st, L.rows, L.nrows, L.blks,
+                       static_cast<const typename Elem<KIND>::T *>(L.data), L.scales, static_cast<const TV *>(L.in0),
+                       L.in1, static_cast<TV *>(L.out0), static_cast<TO1 *>(L.out1));
     return hipGetLastError();
 }
 
@@ -892,27 +1016,16 @@ hipError_t launch_fill_blocks(const Geometry &g, int block_kind, void *blocks, f
     return hipSuccess;
 }
 
-hipError_t launch_reduce_chunks(const ReduceDesc *desc, int64_t n, const void *partials, bool partials_f32, void *out0,
-                                void *out1, bool vec_f64, hipStream_t st, bool add) {
+hipError_t launch_reduce_chunks(const ReduceDesc *desc, int64_t n, const void *partials, void *out0, void *out1,
+                                bool vec_f64, hipStream_t st) {
     if (n <= 0) return hipSuccess;
     const dim3 grid(unsigned((n + 3) / 4)), block(256);
-    auto go = [&](auto tv, auto tp) {   // vector and partial types
-        using TV = decltype(tv);
-        using TP = decltype(tp);
-        auto *o0 = static_cast<TV *>(out0), *o1 = static_cast<TV *>(out1);
-        const TP *pp = static_cast<const TP *>(partials);
-        if (add)
-            hipLaunchKernelGGL((reduce_chunks_kernel<TV, TP, true>), grid, block, 0, st, desc, n, pp, o0, o1);
-        else
-            hipLaunchKernelGGL((reduce_chunks_kernel<TV, TP, false>), grid, block, 0, st, desc, n, pp, o0, o1);
-    };
-    if (vec_f64) {
-        if (partials_f32) go(double(), float());
-        else go(double(), double());
-    } else {
-        if (partials_f32) go(float(), float());
-        else go(float(), double());
-    }
+    if (vec_f64)
+        hipLaunchKernelGGL(reduce_chunks_kernel<double>, grid, block, 0, st, desc, n, static_cast<const double *>(partials),
+                           static_cast<double *>(out0), static_cast<double *>(out1));
+    else
+        hipLaunchKernelGGL(reduce_chunks_kernel<float>, grid, block, 0, st, desc, n, static_cast<const float *>(partials),
+                           static_cast<float *>(out0), static_cast<float *>(out1));
     return hipGetLastError();
 }
 
@@ -967,14 +1080,33 @@ hipError_t launch_transpose_blocks(int kind, const void *src, void *dst, const T
     return hipGetLastError();
 }
 
-hipError_t launch_blockrow(const RowLaunch &L, int kind, bool vec_f64, int phase, hipStream_t st, int out1_f64_in) {
-    const bool out1_f64 = out1_f64_in < 0 ? phase == PHASE_LEAF : out1_f64_in != 0;
-    if (vec_f64) return run_blockrow<ELEM_F64, double, double>(L, phase, st);
+hipError_t launch_stream(const RowLaunch &L, int kind, bool vec_f64, bool out1_f64, hipStream_t st) {
+    if (vec_f64) return run_stream<ELEM_F64, double, double>(L, st);
     if (kind == ELEM_F32)
-        return out1_f64 ? run_blockrow<ELEM_F32, float, double>(L, phase, st)
-                        : run_blockrow<ELEM_F32, float, float>(L, phase, st);
-    return out1_f64 ? run_blockrow<ELEM_BF16, float, double>(L, phase, st)
-                    : run_blockrow<ELEM_BF16, float, float>(L, phase, st);
+        return out1_f64 ? run_stream<ELEM_F32, float, double>(L, st) : run_stream<ELEM_F32, float, float>(L, st);
+    return out1_f64 ? run_stream<ELEM_BF16, float, double>(L, st) : run_stream<ELEM_BF16, float, float>(L, st);
+}
+
+hipError_t launch_sweep(const SweepLaunch &L, bool up, bool vec_f64, hipStream_t st) {
+    if (L.depth < 0 || L.split < 0 || L.depth + L.split > SWEEP_MAX_DEPTH || (L.depth == 0 && !L.leaf)) return hipErrorInvalidValue;
+    const int nb = 1 << L.depth, nw = nb << L.split, vb = vec_f64 ? 8 : 4;
+    const dim3 grid(1u << L.level), block(64u * unsigned(nw));
+    const int slots = 2 * nb - 1;
+    const size_t lds = 64 * size_t(up ? nw * 8 + (L.leaf ? nb : 0) * vb + slots * vb : nw * 8 + (slots + nb) * 8 + slots * vb);
+    if (up) {
+        if (vec_f64)
+            hipLaunchKernelGGL(upsweep_kernel<ELEM_F64>, grid, block, lds, st, L, L.off_leaf, L.off_tr, L.leaf_begin, L.leaf_end);
+        else
+            hipLaunchKernelGGL(upsweep_kernel<ELEM_F32>, grid, block, lds, st, L, L.off_leaf, L.off_tr, L.leaf_begin, L.leaf_end);
+    } else {
+        if (vec_f64)
+            hipLaunchKernelGGL(downsweep_kernel<ELEM_F64>, grid, block, lds, st, L, L.off_leaf, L.off_tr, L.leaf_begin,
+                               L.leaf_end, L.tree_sums, L.near_sums);
+        else
+            hipLaunchKernelGGL(downsweep_kernel<ELEM_F32>, grid, block, lds, st, L, L.off_leaf, L.off_tr, L.leaf_begin,
+                               L.leaf_end, L.tree_sums, L.near_sums);
+    }
+    return hipGetLastError();
 }
 
 namespace {

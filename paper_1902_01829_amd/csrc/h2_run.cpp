@@ -1,5 +1,5 @@
-// The product: y = A x as a fixed sequence of block-row launches over the
-// work lists built at construction (the per-call marshaling of pointer
+// The product: y = A x as a fixed sequence of launches -- the upsweep, one
+// streaming launch over the work list built at construction, the downsweep (the per-call marshaling of pointer
 // batches of Sec. 3.2 becomes static lists), and Y = A X in tiles of
 // right-hand sides on the matrix cores.
 #include "h2_internal.h"
@@ -22,9 +22,8 @@ hipEvent_t take_event(h2_matrix_ &A) {
 // Enqueues the lists in order, with profiling events at phase boundaries
 // when enabled; launch(w) enqueues one list.
 template <class Launch>
-void run_lists(h2_matrix_ &A, const std::vector<WorkList> &lists, hipStream_t st, Launch launch,
-               bool allow_prof = true) {
-    const bool prof = A.prof && allow_prof;
+void run_lists(h2_matrix_ &A, const std::vector<WorkList> &lists, hipStream_t st, Launch launch) {
+    const bool prof = A.prof;
     hipEvent_t ev[PH_COUNT + 1] = {};
     if (prof)
         for (auto &e : ev) e = take_event(A);
@@ -67,123 +66,107 @@ void workspace_bytes(const h2_matrix_ &A, int64_t part[4]) {
 }
 
 void run_product(h2_matrix_ &A, const double *x, double *y, hipStream_t st, const Workspace *ws) {
-    const Workspace own{A.xh, A.yh, A.ynear, nullptr};
+    const Workspace own{A.xh, A.yh, A.ynear, A.lists[0].partials};
     const Workspace &W = ws ? *ws : own;
-    auto row_launch = [&](const WorkList &w) {
+    const WorkList &w = A.lists[0];   // the streaming list
+    const bool prof = A.prof && !ws;
+    hipEvent_t ev[PH_COUNT + 1] = {};
+    if (prof)
+        for (auto &e : ev) e = take_event(A);
+    auto mark = [&](int phase) {   // the start of a phase, or the end of the last
+        if (prof) check_hip(hipEventRecord(ev[phase], st), "hipEventRecord");
+    };
+    const bool cut = !w.slot && w.partials_bytes > 0;
+    auto sweep = [&](const SweepStep &g, bool up) {
+        h2::SweepLaunch L{};
+        L.basis = A.basis;
+        L.off_leaf = up ? A.d_off_VT : A.st.lmin <= A.st.q ? A.d_off_U : nullptr;
+        L.off_tr = up ? A.d_off_FT : A.d_off_E;
+        L.leaf_begin = A.d_leaf_begin;
+        L.leaf_end = A.d_leaf_end;
+        L.x = x;
+        L.y = y;
+        L.tree = up ? W.xh : W.yh;
+        L.near = W.ynear;
+        L.partials = cut ? static_cast<const double *>(W.partials) : nullptr;
+        L.tree_sums = A.d_tree_sums;
+        L.near_sums = A.d_near_sums;
+        L.stride = A.st.rank;
+        L.level = g.level;
+        L.depth = g.depth;
+        L.split = g.split;
+        L.leaf = g.leaf;
+        L.root_done = g.level > A.st.lmin;
+        for (int p = 0; p <= g.depth; ++p) L.rank[p] = A.st.lrank[size_t(g.level + p)];
+        check_hip(h2::launch_sweep(L, up, A.vec_f64, st), "sweep launch");
+    };
+    auto stream_rows = [&](const h2::RowDesc *rows, int64_t nrows, int lds_bytes, hipStream_t on) {
+        if (nrows <= 0) return;
+        h2::RowLaunch L;
+        L.rows = rows;
+        L.nrows = nrows;
+        L.blks = w.blks;
+        L.data = w.data;
+        L.scales = A.scales;
+        L.in0 = W.xh;
+        L.in1 = x;
+        L.out0 = cut ? W.partials : W.yh;
+        L.out1 = cut ? W.partials : W.ynear;
+        L.lds_bytes = lds_bytes;
+        check_hip(h2::launch_stream(L, w.kind, A.vec_f64, cut, on), "stream launch");
+    };
+    // Streamed schedule: the near-field rows of the stream list run on the
+    // handle's second stream, a share from the start of the product and the
+    // rest after the coupling rows; the last launch (leaf phase) waits for them.
+    const bool streamed = A.schedule == H2_SCHEDULE_STREAMED && w.srows;
+    const h2::RowDesc *near_rows = streamed ? w.srows + w.nsrows_coupling : nullptr;
+    int64_t nnear = 0, near_split = 0;
+    if (streamed) {
+        nnear = int64_t(w.near_cum.size()) - 1;
+        const int64_t target = std::llround(A.near_early * double(w.near_cum.back()));
+        near_split = std::lower_bound(w.near_cum.begin(), w.near_cum.end(), target) - w.near_cum.begin();
+        near_split = std::min(near_split, nnear);
+        check_hip(hipEventRecord(A.ev_fork, st), "hipEventRecord");
+        check_hip(hipStreamWaitEvent(A.aux, A.ev_fork, 0), "hipStreamWaitEvent");
+        stream_rows(near_rows, near_split, A.near_lds_bytes, A.aux);
+    }
+    mark(PH_UP);
+    for (const SweepStep &g : A.up_steps) sweep(g, true);
+    mark(PH_STREAM);
+    if (streamed) {
+        stream_rows(w.srows, w.nsrows_coupling, 0, st);
+        check_hip(hipEventRecord(A.ev_mid, st), "hipEventRecord");
+        check_hip(hipStreamWaitEvent(A.aux, A.ev_mid, 0), "hipStreamWaitEvent");
+        stream_rows(near_rows + near_split, nnear - near_split, A.near_lds_bytes, A.aux);
+        check_hip(hipEventRecord(A.ev_join, A.aux), "hipEventRecord");
+    } else if (w.slot) {   // stored by halves: row sums and transposed partials, then their sums
         h2::RowLaunch L;
         L.rows = w.rows;
         L.nrows = w.nrows;
         L.blks = w.blks;
         L.data = w.data;
         L.scales = A.scales;
-        L.in1 = x;
-        L.init = nullptr;
-        L.out1 = nullptr;
-        return L;
-    };
-    // Streamed schedule: the near-field rows of the stream list run on the
-    // handle's second stream, a share from the start of the product and the
-    // rest after the coupling rows; the leaf phase waits for them.
-    const WorkList *sl = nullptr;
-    if (A.schedule == H2_SCHEDULE_STREAMED)
-        for (const WorkList &w : A.lists)
-            if (w.phase == PH_STREAM && w.srows) sl = &w;
-    int64_t nnear = 0, near_split = 0;
-    auto near_launch = [&](int64_t r0, int64_t r1) {
-        if (r1 <= r0) return;
-        h2::RowLaunch L = row_launch(*sl);
-        L.rows = sl->srows + sl->nsrows_coupling + r0;
-        L.nrows = r1 - r0;
         L.in0 = W.xh;
+        L.in1 = x;
         L.out0 = W.yh;
         L.out1 = W.ynear;
-        L.lds_bytes = A.near_lds_bytes;
-        if (sl->red) {
-            L.out0 = L.out1 = ws ? ws->partials : sl->partials;
-            check_hip(h2::launch_blockrow(L, sl->kind, A.vec_f64, PH_STREAM, A.aux, 1), "near-field launch");
-        } else {
-            check_hip(h2::launch_blockrow(L, sl->kind, A.vec_f64, PH_STREAM, A.aux), "near-field launch");
-        }
-    };
-    if (sl) {
-        nnear = int64_t(sl->near_cum.size()) - 1;
-        const int64_t target = std::llround(A.near_early * double(sl->near_cum.back()));
-        near_split = std::lower_bound(sl->near_cum.begin(), sl->near_cum.end(), target) - sl->near_cum.begin();
-        near_split = std::min(near_split, nnear);
-        check_hip(hipEventRecord(A.ev_fork, st), "hipEventRecord");
-        check_hip(hipStreamWaitEvent(A.aux, A.ev_fork, 0), "hipStreamWaitEvent");
-        near_launch(0, near_split);
+        check_hip(h2::launch_stream_half(L, w.groups, w.ngroups, w.slot, w.gslot, W.partials, w.kind, A.vec_f64, st),
+                  "half-storage stream launch");
+        check_hip(h2::launch_reduce_chunks(w.red, w.nred, W.partials, W.yh, W.ynear, A.vec_f64, st),
+                  "partial sum launch");
+    } else {
+        stream_rows(w.rows, w.nrows, 0, st);
     }
-    run_lists(A, A.lists, st, [&](const WorkList &w) {
-        void *partials = ws ? ws->partials : w.partials;
-        h2::RowLaunch L = row_launch(w);
-        if (&w == sl) {
-            // coupling rows here; the rest of the near field on the second stream
-            L.rows = sl->srows;
-            L.nrows = sl->nsrows_coupling;
-            L.in0 = W.xh;
-            L.out0 = W.yh;
-            L.out1 = W.ynear;
-            if (w.red) {
-                L.out0 = L.out1 = partials;
-                check_hip(h2::launch_blockrow(L, w.kind, A.vec_f64, int(w.phase), st, 1), "blockrow launch");
-                check_hip(h2::launch_reduce_chunks(w.sred, w.nsred_coupling, partials, false, W.yh, W.ynear,
-                                                   A.vec_f64, st),
-                          "chunk sum launch");
-            } else {
-                check_hip(h2::launch_blockrow(L, w.kind, A.vec_f64, int(w.phase), st), "blockrow launch");
-            }
-            check_hip(hipEventRecord(A.ev_mid, st), "hipEventRecord");
-            check_hip(hipStreamWaitEvent(A.aux, A.ev_mid, 0), "hipStreamWaitEvent");
-            near_launch(near_split, nnear);
-            if (w.red)
-                check_hip(h2::launch_reduce_chunks(w.sred + w.nsred_coupling, w.nred - w.nsred_coupling, partials,
-                                                   false, W.yh, W.ynear, A.vec_f64, A.aux),
-                          "chunk sum launch");
-            check_hip(hipEventRecord(A.ev_join, A.aux), "hipEventRecord");
-            return;
+    mark(PH_DOWN);
+    for (const SweepStep &g : A.down_steps) {
+        if (g.leaf) {
+            mark(PH_LEAF);
+            if (streamed) check_hip(hipStreamWaitEvent(st, A.ev_join, 0), "hipStreamWaitEvent");
         }
-        if (sl && w.phase == PH_LEAF) check_hip(hipStreamWaitEvent(st, A.ev_join, 0), "hipStreamWaitEvent");
-        switch (w.phase) {
-            case PH_UP:
-                L.in0 = W.xh;
-                L.out0 = W.xh;
-                break;
-            case PH_STREAM:
-                L.in0 = W.xh;
-                L.out0 = W.yh;
-                L.out1 = W.ynear;
-                if (w.slot) {   // stored by halves: row sums and transposed partials, then their sums
-                    check_hip(h2::launch_stream_half(L, w.groups, w.ngroups, w.slot, w.gslot, partials, w.kind,
-                                                     A.vec_f64, st),
-                              "half-storage stream launch");
-                    check_hip(h2::launch_reduce_chunks(w.red, w.nred, partials, !A.vec_f64, W.yh, W.ynear, A.vec_f64,
-                                                       st, true),
-                              "partial sum launch");
-                    return;
-                }
-                if (w.red) {   // chunks of a split list: partial sums, then their sums per row
-                    L.out0 = L.out1 = partials;
-                    check_hip(h2::launch_blockrow(L, w.kind, A.vec_f64, int(w.phase), st, 1), "blockrow launch");
-                    check_hip(h2::launch_reduce_chunks(w.red, w.nred, partials, false, W.yh, W.ynear, A.vec_f64, st),
-                              "chunk sum launch");
-                    return;
-                }
-                break;
-            case PH_DOWN:
-                L.in0 = W.yh;
-                L.init = W.yh;
-                L.out0 = W.yh;
-                break;
-            default:
-                L.in0 = W.yh;
-                L.init = W.ynear;
-                L.out0 = W.yh;
-                L.out1 = y;
-                break;
-        }
-        check_hip(h2::launch_blockrow(L, w.kind, A.vec_f64, int(w.phase), st), "blockrow launch");
-    }, ws == nullptr);
+        sweep(g, false);
+    }
+    mark(PH_COUNT);
+    if (prof) A.pending.insert(A.pending.end(), ev, ev + PH_COUNT + 1);
 }
 
 // One pass of up to MM_TILE right-hand sides on the matrix cores.

@@ -63,6 +63,14 @@ void adopt(h2_matrix_ &A, h2_matrix_ &B) {
     std::swap(A.yh, B.yh);
     std::swap(A.ynear, B.ynear);
     std::swap(A.lists, B.lists);
+    std::swap(A.up_steps, B.up_steps);
+    std::swap(A.down_steps, B.down_steps);
+    std::swap(A.d_off_U, B.d_off_U);
+    std::swap(A.d_off_VT, B.d_off_VT);
+    std::swap(A.d_off_E, B.d_off_E);
+    std::swap(A.d_off_FT, B.d_off_FT);
+    std::swap(A.d_tree_sums, B.d_tree_sums);
+    std::swap(A.d_near_sums, B.d_near_sums);
     std::swap(A.mm_lists, B.mm_lists);
     std::swap(A.mm_host_rows, B.mm_host_rows);
     std::swap(A.mm_host_blks, B.mm_host_blks);
@@ -128,10 +136,10 @@ void orthogonalize(h2_matrix_ &A, hipStream_t st) {
     L.T = static_cast<double *>(scratch.alloc((s.nnodes * int64_t(kmax) * kmax + h2::PROJ_T_PAD) * 8));
     if (!A.symmetric)
         L.T_col = static_cast<double *>(scratch.alloc((s.nnodes * int64_t(kmax) * kmax + h2::PROJ_T_PAD) * 8));
-    L.off_U = scratch.upload(A.off_U, st);
-    L.off_VT = scratch.upload(A.off_VT, st);
-    L.off_E = scratch.upload(A.off_E, st);
-    L.off_FT = scratch.upload(A.off_FT, st);
+    L.off_U = A.d_off_U;
+    L.off_VT = A.d_off_VT;
+    L.off_E = A.d_off_E;
+    L.off_FT = A.d_off_FT;
     L.leaf_begin = A.d_leaf_begin;
     L.leaf_end = A.d_leaf_end;
     L.proj = scratch.upload(proj, st);
@@ -319,8 +327,8 @@ void compress(h2_matrix_ &A, double eps, hipStream_t st, int *ranks_out) {
             h2::CompLaunch L{};
             L.basis = static_cast<const double *>(A.basis);
             L.blocks = static_cast<const double *>(A.blocks);
-            L.off_U = scratch.upload(column_tree ? A.off_VT : A.off_U, st);
-            L.off_E = scratch.upload(column_tree ? A.off_FT : A.off_E, st);
+            L.off_U = column_tree ? A.d_off_VT : A.d_off_U;
+            L.off_E = column_tree ? A.d_off_FT : A.d_off_E;
             L.b_t = L.x_t = column_tree ? 1 : 0;
             L.leaf_begin = A.d_leaf_begin;
             L.leaf_end = A.d_leaf_end;

@@ -1,7 +1,7 @@
-"""The streaming launch at the edges of its steps: ranks from 1 to 64 (lane
+"""The streaming launch and the tree sweeps at the edges of their steps: ranks from 1 to 64 (lane
 groups of 64 / R rows, widths that are no multiple of a 16-byte item), leaves
 from one point up, rows of more than 64 blocks, and lists cut into pieces or
-not, in the three storages, against the oracle's exact product of the stored values."""
+not, sweeps of one to several levels per launch, in the three storages, against the oracle's exact product of the stored values."""
 import numpy as np
 import pytest
 
@@ -15,7 +15,8 @@ pytestmark = pytest.mark.gpu
 TOL = {0: 1e-12, 1: 1e-6, 2: 1e-6}
 
 CASES = [(3, 2, 2, 1), (200, 2, 7, 2), (900, 3, 3, 2), (2100, 2, 33, 5), (1500, 3, 31, 3), (2500, 2, 63, 7),
-         (1300, 2, 50, 8), (9000, 3, 20, 3)]
+         (1300, 2, 50, 8), (9000, 3, 20, 3),
+         (6000, 2, 3, 1), (5000, 2, 9, 3), (4000, 2, 60, 6)]
 
 
 @pytest.mark.parametrize("storage", [0, 1, 2], ids=["fp64", "fp32", "bf16"])
