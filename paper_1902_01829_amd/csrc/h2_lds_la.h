@@ -77,7 +77,8 @@ __device__ __forceinline__ void qr_reflect(const double (&v)[MR], double tau, do
 // The caller's array holds (MAXM + QR_PAD) x 64 doubles or more.  The step
 // of column c is serial (one wavefront's four lanes), so it is kept short:
 // no masks on rows past M, R(c, c) in a register of its own.
-template <int MAXM = QR_MAXM>
+// With FORM_Q false, A is left undefined.
+template <int MAXM = QR_MAXM, bool FORM_Q = true>
 __device__ __forceinline__ void householder_qr(double *A, double *tau, double *sgn, int M, int N, double *T, int ldt) {
     static_assert(MAXM % 4 == 0 && MAXM <= QR_MAXM, "rows per thread");
     constexpr int MR = MAXM / 4, LDV = MAXM + QR_PAD;
@@ -139,6 +140,10 @@ __device__ __forceinline__ void householder_qr(double *A, double *tau, double *s
             if (r < N) T[int64_t(col) * ldt + r] = r < col ? sgn[r] * a[i] : (r == col ? sgn[col] * rcc : 0.0);
         }
     }
+    if constexpr (!FORM_Q) {
+        __syncthreads();
+        return;
+    }
     // column col of Q: H_col .. H_0 applied in reverse order to e_col
     if (mine) {
 #pragma unroll
@@ -174,10 +179,25 @@ __device__ inline double dpp_sum16(double v) {   // over the 16 lanes of a DPP r
     return v;
 }
 
+// In-place transposition of the n x n matrix A (column-major, leading
+// dimension ld, LDS) by the whole workgroup.
+__device__ inline void transpose_square(double *A, int ld, int n) {
+    for (int i = threadIdx.x; i < n * n; i += blockDim.x) {
+        const int c = i / n, r = i - c * n;
+        if (r < c) {
+            const double x = A[c * ld + r];
+            A[c * ld + r] = A[r * ld + c];
+            A[r * ld + c] = x;
+        }
+    }
+    __syncthreads();
+}
+
 // One-sided (Hestenes) Jacobi SVD.  G is the L x n matrix (column-major,
 // leading dimension ldg, LDS) whose columns are the rows of the matrix B to
 // decompose (G = B^T); Y (n x n, leading dimension ldy, LDS) starts as the
-// identity.  Plane rotations applied to pairs of columns of G and Y make the
+// identity, or as the orthogonal matrix Q that G has been multiplied by from
+// the right beforehand.  Plane rotations applied to pairs of columns of G and Y make the
 // columns of G mutually orthogonal, so that G_0 Y = G and B = Y diag(s) V^T
 // with s_j = |column j of G|: the columns of Y are left singular vectors of
 // B, orthonormal to rounding also where s_j = 0.  Pairs are visited in the
