@@ -7,7 +7,7 @@
 // are not symmetric, the blocks S_ji of its block column follow, since the
 // one basis tree serves the columns too) and keeps the triangular factor R_i
 // of its QR factorization.  The stack is not formed
-// whole: a workgroup holds 128 x 64 in registers, so blocks are appended
+// whole: a workgroup holds 512 x 64 in registers, so blocks are appended
 // under the current factor and folded into it with a QR of the stack
 // whenever the next block would not fit (the same R up to row signs, which
 // the truncation does not see: it uses R only through R^T R).
@@ -32,7 +32,7 @@
 // singular values at least eps times its largest; the host takes the
 // largest count of a level as its new rank.
 //
-// One workgroup per node: 512 threads with the stack in registers for the
+// One workgroup per node: 1024 threads with the stack in registers for the
 // basis generation, 256 threads with every matrix staged column-major in LDS
 // for the truncation.
 
@@ -57,135 +57,248 @@ constexpr int JACOBI_SWEEPS = 30;
 
 __device__ inline int64_t level_first(int l) { return (int64_t(1) << l) - 1; }
 
-// Basis generation of one node, a 256 x k stack held in registers of a
-// 1024-thread workgroup: wave w owns columns 4 w .. 4 w + 3, lanes
-// 16 h .. 16 h + 15 of it column 4 w + h, and lane j = l % 16 of those rows
-// j, j + 16, ..., j + 240 (a[i] = row j + 16 i; consecutive lanes touch
-// consecutive LDS words).  Rows 0 .. 63 (i < 4) hold the current triangular
-// factor (first: the parent term), rows 64 .. 255 the coupling blocks
-// appended since (as many k-row blocks as fit).  A fold is a Householder QR
-// without Q over all 256 rows: per column c the sixteen lanes of column c
-// form the reflector and publish it in LDS (double buffered, so one barrier
-// per column), and every lane of a later column applies it to its 16 rows;
-// entries below the diagonal are set to zero as they are eliminated, so
-// after a fold rows k .. 255 are zero.  The lanes of a column are one DPP
-// row, so their sums are four DPP moves.  Register arrays are indexed
-// statically only (the diagonal row is selected by comparison).
-constexpr int BG_THREADS = 1024, BG_ROWS = 16, BG_STACK = 256, BG_TLD = 65;
+// Basis generation of one node, a 512 x k stack held in registers of a
+// 1024-thread workgroup: wave w owns columns w, w + 16, w + 32, w + 48 (NS of
+// them; a[s] = column w + 16 s) and lane l of it rows l + 64 i (a[s][i]).
+// Rows 0 .. 63 hold the current triangular factor (first: the parent term),
+// rows 64 .. 511 the coupling blocks appended since (as many k-row blocks as
+// fit).  A fold is a Householder QR without Q over these rows: step c reads
+// reflector c from LDS (double buffered, one barrier per step), and the wave
+// of column c + 1 applies it to that column first and publishes reflector
+// c + 1 while the others still apply reflector c.  Entries below the diagonal
+// are set to zero as they are eliminated, so after a fold rows k .. 511 are
+// zero.  Register arrays are indexed statically only.
+//
+// Bound by the serial chain of a step (reduction over the wave, square root,
+// division, barrier), so steps are few and short: 448 new rows share one
+// pass over the columns, a reflector's LDS read serves four columns, and
+// their four sums go through one reduction (the halves of two columns are
+// exchanged, then the 16-lane rows, so that each row of 16 lanes ends with
+// one column).  Columns are dealt in turn, so every wave has work until the
+// last ones.  A 2^16-point 2-D build at rank 64: 9.3 -> 4.1 ms over its
+// levels (before: 192 new rows per pass, four adjacent columns per wave with
+// 16 rows per lane, a reflector read whole by every wave: LDS-bound).
+constexpr int BG_THREADS = 1024, BG_ROWS = 8, BG_FIT = 64 * (BG_ROWS - 1), BG_STAGE = 128, BG_TLD = 65;
 
-__device__ inline void fold_r(double (&a)[BG_ROWS], int k, int col, int j, double (*vbuf)[BG_STACK],
-                              double *tbuf) {
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int c = 0; c < k; ++c) {
-        double *v = vbuf[c & 1];
-        if (wv == (c >> 2) && (lane >> 4) == (c & 3)) {   // the sixteen lanes of column c
-            double sq = 0.0, al = 0.0;
-#pragma unroll
-            for (int i = 0; i < BG_ROWS; ++i) {
-                const int r = j + 16 * i;
-                sq += r > c ? a[i] * a[i] : 0.0;
-                al += r == c ? a[i] : 0.0;
-            }
-            sq = dpp_sum16(sq);
-            al = dpp_sum16(al);
-            const double nrm = sqrt(sq + al * al);
-            double beta = al, tc = 0.0, sc = 0.0;
-            if (sq > 0.0) {
-                beta = al >= 0.0 ? -nrm : nrm;
-                tc = (beta - al) / beta;
-                sc = 1.0 / (al - beta);
-            }
-#pragma unroll
-            for (int i = 0; i < BG_ROWS; ++i) {
-                const int r = j + 16 * i;
-                v[r] = r > c ? a[i] * sc : (r == c ? 1.0 : 0.0);
-                a[i] = r > c ? 0.0 : (r == c ? beta : a[i]);
-            }
-            if (j == 0) tbuf[c & 1] = tc;
-        }
-        __syncthreads();
-        const double tc = tbuf[c & 1];
-        if (col > c && col < k && tc != 0.0) {   // uniform over the sixteen lanes of a column
-            double d = 0.0;
-#pragma unroll
-            for (int i = 0; i < BG_ROWS; ++i) d += v[j + 16 * i] * a[i];
-            d = dpp_sum16(d) * tc;
-#pragma unroll
-            for (int i = 0; i < BG_ROWS; ++i) a[i] -= d * v[j + 16 * i];
-        }
+struct StackLds {
+    double v[2][64 * BG_ROWS], tau[2];
+    int64_t off[BG_FIT];             // the appended blocks' offsets
+    double tile[BG_STAGE * BG_TLD];  // staged blocks, row-major; first R_parent and E_i
+};
+
+// x of one half of the wave added to the other half, y likewise: lanes 0 ..
+// 31 get x, lanes 32 .. 63 y (WIDTH 32); even 16-lane rows x, odd rows y
+// (WIDTH 16).
+template <int WIDTH>
+__device__ inline double swap_add(double x, double y) {
+    const uint64_t xb = uint64_t(__double_as_longlong(x)), yb = uint64_t(__double_as_longlong(y));
+    uint64_t p, q;
+    if constexpr (WIDTH == 32) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(uint32_t(xb), uint32_t(yb), false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(uint32_t(xb >> 32), uint32_t(yb >> 32), false, false);
+        p = (uint64_t(hi[0]) << 32) | lo[0];
+        q = (uint64_t(hi[1]) << 32) | lo[1];
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(uint32_t(xb), uint32_t(yb), false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(uint32_t(xb >> 32), uint32_t(yb >> 32), false, false);
+        p = (uint64_t(hi[0]) << 32) | lo[0];
+        q = (uint64_t(hi[1]) << 32) | lo[1];
     }
-    __syncthreads();   // the last reflector's readers are done before vbuf is reused
+    return __longlong_as_double(int64_t(p)) + __longlong_as_double(int64_t(q));
 }
 
+__device__ inline double lane_value(double x, int l) {   // lane l's x, l uniform
+    const int64_t b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_readlane(int(b), l), hi = __builtin_amdgcn_readlane(int(b >> 32), l);
+    return __longlong_as_double((int64_t(hi) << 32) | uint32_t(lo));
+}
+
+// The sums over the wave of N <= 4 values, in every lane.
+template <int N>
+__device__ __forceinline__ void wave_sums(double (&d)[N]) {
+    const double e = swap_add<32>(d[0], d[N > 1 ? 1 : 0]);
+    if constexpr (N <= 2) {   // rows of 16 lanes: 0 0 1 1
+        const double f = dpp_sum16(swap_add<16>(e, e));
+        if constexpr (N == 1) {
+            d[0] = f;
+        } else {
+            d[0] = lane_value(f, 0);
+            d[1] = lane_value(f, 32);
+        }
+    } else {                  // rows of 16 lanes: 0 2 1 3
+        const double f = dpp_sum16(swap_add<16>(e, swap_add<32>(d[2], d[N - 1])));
+        d[0] = lane_value(f, 0);
+        d[1] = lane_value(f, 32);
+        d[2] = lane_value(f, 16);
+        if constexpr (N == 4) d[3] = lane_value(f, 48);
+    }
+}
+
+// The reflector of column c (x, the wave's rows of it), left in v and tau.
+template <int NI>
+__device__ __forceinline__ void publish(double (&x)[BG_ROWS], int c, int lane, double *v, double *tau) {
+    double sq[1] = {lane > c ? x[0] * x[0] : 0.0};
+#pragma unroll
+    for (int i = 1; i < NI; ++i) sq[0] += x[i] * x[i];
+    wave_sums<1>(sq);
+    const double al = lane_value(x[0], c), nrm = sqrt(sq[0] + al * al);
+    double beta = al, tc = 0.0, sc = 0.0;
+    if (sq[0] > 0.0) {
+        beta = al >= 0.0 ? -nrm : nrm;
+        tc = (beta - al) / beta;
+        sc = 1.0 / (al - beta);
+    }
+    v[lane] = lane > c ? x[0] * sc : (lane == c ? 1.0 : 0.0);
+    x[0] = lane > c ? 0.0 : (lane == c ? beta : x[0]);
+#pragma unroll
+    for (int i = 1; i < NI; ++i) {
+        v[lane + 64 * i] = x[i] * sc;
+        x[i] = 0.0;
+    }
+    if (lane == 0) *tau = tc;
+}
+
+// Steps c = 16 S .. 16 S + 15 of a fold, then those of the next slot.
+template <int NS, int NI, int S>
+__device__ __forceinline__ void fold_slot(double (&a)[NS][BG_ROWS], int k, int wv, int lane, StackLds &s) {
+    if constexpr (S < NS) {
+#pragma unroll 1
+        for (int cc = 0; cc < 16 && 16 * S + cc < k; ++cc) {
+            const int c = 16 * S + cc;
+            __syncthreads();   // reflector c is published; reflector c - 1 has been read
+            double v[NI], d[NS - S];
+#pragma unroll
+            for (int i = 0; i < NI; ++i) v[i] = s.v[c & 1][lane + 64 * i];
+            const double tc = s.tau[c & 1];
+#pragma unroll
+            for (int n = S; n < NS; ++n) {
+                d[n - S] = 0.0;
+                if (n > S || wv > cc) {   // the wave's columns to the right of c
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) d[n - S] += v[i] * a[n][i];
+                }
+            }
+            wave_sums<NS - S>(d);
+#pragma unroll
+            for (int n = S; n < NS; ++n) {
+                if (n > S || wv > cc) {
+                    d[n - S] *= tc;
+#pragma unroll
+                    for (int i = 0; i < NI; ++i) a[n][i] -= d[n - S] * v[i];
+                    if (n <= S + 1 && 16 * n + wv == c + 1 && c + 1 < k)
+                        publish<NI>(a[n], c + 1, lane, s.v[(c + 1) & 1], &s.tau[(c + 1) & 1]);
+                }
+            }
+        }
+        fold_slot<NS, NI, S + 1>(a, k, wv, lane, s);
+    }
+}
+
+template <int NS, int NI>
+__device__ __forceinline__ void fold_r(double (&a)[NS][BG_ROWS], int k, int wv, int lane, StackLds &s) {
+    if (wv == 0) publish<NI>(a[0], 0, lane, s.v[0], &s.tau[0]);
+    fold_slot<NS, NI, 0>(a, k, wv, lane, s);
+    __syncthreads();   // the last reflectors are read before they are overwritten
+}
+
+template <int NS>
 __global__ __launch_bounds__(BG_THREADS) void basis_generation_kernel(CompLaunch L, int level, int k, int kp,
                                                                       int parent_term) {
-    __shared__ double vbuf[2][BG_STACK], tbuf[2];
-    __shared__ double tile[64 * BG_TLD];   // staging of R_parent (column-major) and of each coupling block (row-major)
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int col = 4 * wv + (lane >> 4), j = lane & 15;
+    __shared__ StackLds s;
+    const int t = threadIdx.x, lane = t & 63, wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int64_t node = level_first(level) + blockIdx.x;
-    double a[BG_ROWS];
+    double a[NS][BG_ROWS];
 #pragma unroll
-    for (int i = 0; i < BG_ROWS; ++i) a[i] = 0.0;
+    for (int n = 0; n < NS; ++n)
+#pragma unroll
+        for (int i = 0; i < BG_ROWS; ++i) a[n][i] = 0.0;
     bool dirty = false;   // rows hold entries not yet folded into a triangular factor
     if (parent_term) {    // rows 0 .. kp-1: P = R_parent E_i^T (kp x k), R_parent upper triangular
         const double *Rp = L.R + ((node - 1) >> 1) * L.kmax * L.kmax;   // zero below its diagonal
+        const double *E = L.basis + L.off_E[node];                      // k x kp (or its transpose)
+        double *Et = s.tile + 64 * BG_TLD;
         for (int i = t; i < 64 * kp; i += BG_THREADS) {
-            const int c = i >> 6, r = i & 63;
-            tile[c * BG_TLD + r] = r < kp ? Rp[int64_t(c) * L.kmax + r] : 0.0;
+            const int u = i >> 6, r = i & 63;
+            s.tile[u * BG_TLD + r] = r < kp ? Rp[int64_t(u) * L.kmax + r] : 0.0;
+            if (r < k) Et[u * BG_TLD + r] = L.x_t ? E[at2(kp, u, r)] : E[at2(k, r, u)];
         }
         __syncthreads();
-        const double *E = L.basis + L.off_E[node];   // k x kp (or its transpose)
-        if (col < k)
-            for (int u = 0; u < kp; ++u) {
-                const double e = L.x_t ? E[at2(kp, u, col)] : E[at2(k, col, u)];
+        for (int u = 0; u < kp; ++u) {
+            const double x = s.tile[u * BG_TLD + lane];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) a[i] += tile[u * BG_TLD + j + 16 * i] * e;
-            }
+            for (int n = 0; n < NS; ++n)
+                if (wv + 16 * n < k) a[n][0] += x * Et[u * BG_TLD + wv + 16 * n];
+        }
         dirty = true;
     }
     // the stack's blocks: those of block row i, transposed, then (when the
     // coupling blocks are not symmetric) those of block column i as they are
     const int64_t nrow = L.use_rows ? L.row_start[node + 1] - L.row_start[node] : 0;
     const int64_t nb = nrow + (L.columns ? L.col_start[node + 1] - L.col_start[node] : 0);
-    const int ng = (k + 1) >> 1;
-    int64_t b = 0;
-    for (;;) {   // append as many blocks as fit under the factor, then fold (one call site)
-        for (int bot = 0; b < nb && bot + k <= BG_STACK - 64; ++b, bot += k) {
-            __syncthreads();   // the tile's previous contents are consumed
-            const bool from_row = b < nrow;
-            const double *S = L.blocks + (from_row ? L.blk[L.row_start[node] + b].off
-                                                   : L.col_blk[L.col_start[node] + (b - nrow)]);
-            for (int i = t; i < ng * k; i += BG_THREADS) {   // S(r, 2g .. 2g+1) is one 16-byte item
-                const int g = i / k, r = i - g * k;
-                const f64x2 v = *reinterpret_cast<const f64x2 *>(S + (int64_t(g) * k + r) * 2);
-                tile[r * BG_TLD + 2 * g] = v.x;
-                tile[r * BG_TLD + 2 * g + 1] = v.y;   // column k when k is odd: padding, never read
-            }
-            __syncthreads();
-            // rows 64 + bot .. 64 + bot + k - 1: row rr, column col is S(col, rr) for a row block
-            // (S^T) and S(rr, col) for a column block
-            if (col < k) {
+    const int ng = (k + 1) >> 1, items = ng * k, stage = BG_STAGE / k;   // stage: blocks staged at a time
+    const float per_k = 1.0f / float(k);   // (x + 1/2) / k is at least 1/128 away from a whole number
+    const float per_items = 1.0f / float(items);
+    for (int64_t b = 0;;) {   // append as many blocks as fit under the factor, then fold
+        const int fit = int(nb - b < BG_FIT / k ? nb - b : BG_FIT / k);
+        __syncthreads();   // the previous offsets and tile are consumed
+        if (t < fit) {
+            const int64_t e = b + t;
+            s.off[t] = e < nrow ? L.blk[L.row_start[node] + e].off : L.col_blk[L.col_start[node] + (e - nrow)];
+        }
+        __syncthreads();
+        for (int f = 0; f < fit; f += stage) {
+            const int cnt = fit - f < stage ? fit - f : stage;
+            int e0 = t;
+            asm volatile("" : "+v"(e0));   // the items' places are computed here each time, not kept across folds
+            f64x2 x[BG_STAGE * 32 / BG_THREADS];   // cnt items <= stage ng k <= 128 * 32 (k = 1: 128)
+            int at[BG_STAGE * 32 / BG_THREADS];
 #pragma unroll
-                for (int i = 4; i < BG_ROWS; ++i) {
-                    const int rr = j + 16 * i - 64 - bot;
-                    if (rr >= 0 && rr < k) a[i] = from_row ? tile[col * BG_TLD + rr] : tile[rr * BG_TLD + col];
+            for (int m = 0; m < BG_STAGE * 32 / BG_THREADS; ++m) {   // S(r, 2g .. 2g+1) is one 16-byte item
+                const int e = e0 + BG_THREADS * m;
+                at[m] = -1;
+                if (e < cnt * items) {
+                    const int bi = int((float(e) + 0.5f) * per_items), w = e - bi * items;
+                    const int g = int((float(w) + 0.5f) * per_k), r = w - g * k;
+                    x[m] = *reinterpret_cast<const f64x2 *>(L.blocks + s.off[f + bi] + (int64_t(g) * k + r) * 2);
+                    at[m] = (bi * k + r) * BG_TLD + 2 * g;
                 }
             }
-            dirty = true;
+            if (f > 0) __syncthreads();   // the tile's previous contents are consumed
+#pragma unroll
+            for (int m = 0; m < BG_STAGE * 32 / BG_THREADS; ++m)
+                if (at[m] >= 0) {
+                    s.tile[at[m]] = x[m].x;
+                    s.tile[at[m] + 1] = x[m].y;   // column k when k is odd: padding, never read
+                }
+            __syncthreads();
+            // row 64 + f k + y k + rr, column col is S(col, rr) of block y for a row block (S^T) and
+            // S(rr, col) for a column block
+#pragma unroll
+            for (int i = 1; i < BG_ROWS; ++i) {
+                const int q = lane + 64 * (i - 1) - f * k;
+                if (q >= 0 && q < cnt * k) {
+                    const int y = int((float(q) + 0.5f) * per_k), rr = q - y * k;
+                    const bool from_row = b + f + y < nrow;
+                    const double *S = s.tile + y * k * BG_TLD + (from_row ? rr : rr * BG_TLD);
+                    const int step = from_row ? BG_TLD : 1;
+#pragma unroll
+                    for (int n = 0; n < NS; ++n)
+                        if (wv + 16 * n < k) a[n][i] = S[(wv + 16 * n) * step];
+                }
+            }
         }
-        if (!dirty) break;
-        fold_r(a, k, col, j, vbuf, tbuf);
+        b += fit;
+        if (fit == 0 && !dirty) break;
+        if (fit * k <= 192) fold_r<NS, 4>(a, k, wv, lane, s);
+        else fold_r<NS, BG_ROWS>(a, k, wv, lane, s);
         dirty = false;
         if (b >= nb) break;
     }
     double *R = L.R + node * L.kmax * L.kmax;   // rows 0 .. k-1 (zero below the diagonal)
-    if (col < k) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = j + 16 * i;
-            if (r < k) R[int64_t(col) * L.kmax + r] = a[i];
-        }
+    for (int n = 0; n < NS; ++n) {
+        const int col = wv + 16 * n;
+        if (col < k && lane < k) R[int64_t(col) * L.kmax + lane] = a[n][0];
     }
 }
 
@@ -448,7 +561,10 @@ __global__ __launch_bounds__(256) void place_kernel(const double *src, double *d
 
 hipError_t launch_basis_generation(const CompLaunch &L, int level, int k, int kp, bool parent_term, hipStream_t st) {
     if (k < 1 || k > QR_MAXN || kp > QR_MAXN || (parent_term && kp < 1)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(basis_generation_kernel, dim3(unsigned(int64_t(1) << level)), dim3(BG_THREADS), 0, st, L,
+    auto *kernel = k <= 16 ? basis_generation_kernel<1>
+                 : k <= 32 ? basis_generation_kernel<2>
+                 : k <= 48 ? basis_generation_kernel<3> : basis_generation_kernel<4>;
+    hipLaunchKernelGGL(kernel, dim3(unsigned(int64_t(1) << level)), dim3(BG_THREADS), 0, st, L,
                        level, k, kp, parent_term ? 1 : 0);
     return hipGetLastError();
 }
