@@ -319,22 +319,23 @@ void build_device(h2_matrix_ &A, const h2_arrays *src, hipStream_t stream) {
         DeviceArena scratch;   // geometry and fill lists, freed after the build
         if (A.mem.cap >= 0) scratch.cap = std::max<int64_t>(0, A.mem.cap - A.mem.bytes);
         h2::Geometry g;
-        g.pts = scratch.upload(s.pts, stream);
-        g.lo = scratch.upload(s.lo, stream);
-        g.hi = scratch.upload(s.hi, stream);
-        g.begin = scratch.upload(s.begin, stream);
-        g.end = scratch.upload(s.end, stream);
-        g.cheb = scratch.upload(cheb, stream);
+        g.pts = scratch.stage(s.pts, stream);
+        g.lo = scratch.stage(s.lo, stream);
+        g.hi = scratch.stage(s.hi, stream);
+        g.begin = scratch.stage(s.begin, stream);
+        g.end = scratch.stage(s.end, stream);
+        g.cheb = scratch.stage(cheb, stream);
         g.dim = s.dim;
         g.cheb_p = s.cheb_p;
         g.rank = k;
         g.corr_len = s.corr_len;
-        const int64_t *d_leaf = scratch.upload(leaf_node, stream);
-        const int64_t *d_offU = scratch.upload(off_U, stream);
-        const int64_t *d_offVT = scratch.upload(off_VT, stream);
-        const int64_t *d_offE = scratch.upload(off_E, stream);
-        const int64_t *d_offFT = scratch.upload(off_FT, stream);
-        const h2::FillDesc *d_fill = scratch.upload(fill, stream);
+        const int64_t *d_leaf = scratch.stage(leaf_node, stream);
+        const int64_t *d_offU = scratch.stage(off_U, stream);
+        const int64_t *d_offVT = scratch.stage(off_VT, stream);
+        const int64_t *d_offE = scratch.stage(off_E, stream);
+        const int64_t *d_offFT = scratch.stage(off_FT, stream);
+        const h2::FillDesc *d_fill = scratch.stage(fill, stream);
+        scratch.flush(stream);
         check_hip(h2::launch_fill_bases(g, bk, A.basis, d_leaf, d_offU, d_offVT, nleaves, d_offE, d_offFT,
                                         lowrank ? s.nnodes : 0, stream),
                   "fill bases");
@@ -536,12 +537,12 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
         w.kind = kind;
         w.data = data;
         w.nrows = int64_t(e.rows.size());
-        w.rows = A.mem.upload(e.rows, stream);
-        w.blks = A.mem.upload(e.blks, stream);
+        w.rows = A.mem.stage(e.rows, stream);
+        w.blks = A.mem.stage(e.blks, stream);
         if (enc == 1) {
-            w.items = A.mem.upload(e.items, stream);
+            w.items = A.mem.stage(e.items, stream);
             w.nitems = int64_t(e.items.size());
-            w.pitems = A.mem.upload(e.pitems, stream);
+            w.pitems = A.mem.stage(e.pitems, stream);
             w.npitems = int64_t(e.pitems.size());
         }
         (enc == 0 ? A.lists : A.mm_lists).push_back(w);
@@ -803,13 +804,13 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             w.kind = sk;
             w.data = A.blocks;
             w.nrows = int64_t(rows.size());
-            w.rows = A.mem.upload(rows, stream);
-            w.blks = A.mem.upload(blks, stream);
-            w.slot = A.mem.upload(slots, stream);
-            w.groups = A.mem.upload(hg, stream);
+            w.rows = A.mem.stage(rows, stream);
+            w.blks = A.mem.stage(blks, stream);
+            w.slot = A.mem.stage(slots, stream);
+            w.groups = A.mem.stage(hg, stream);
             w.ngroups = int64_t(hg.size());
-            w.gslot = A.mem.upload(gslot, stream);
-            w.red = A.mem.upload(red, stream);
+            w.gslot = A.mem.stage(gslot, stream);
+            w.red = A.mem.stage(red, stream);
             w.nred = int64_t(red.size());
             w.partials_bytes = int64_t(ents.size()) * 64 * (A.vec_f64 ? 8 : 4);
             w.partials = A.mem.alloc(w.partials_bytes);
@@ -894,10 +895,10 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             w.kind = sk;
             w.data = A.blocks;
             w.nrows = int64_t(rows.size());
-            w.rows = A.mem.upload(rows, stream);
-            w.blks = A.mem.upload(blks, stream);
-            A.d_tree_sums = A.mem.upload(tree_sums, stream);
-            A.d_near_sums = A.mem.upload(near_sums, stream);
+            w.rows = A.mem.stage(rows, stream);
+            w.blks = A.mem.stage(blks, stream);
+            A.d_tree_sums = A.mem.stage(tree_sums, stream);
+            A.d_near_sums = A.mem.stage(near_sums, stream);
             w.partials_bytes = w.nrows * 64 * 8;
             w.partials = A.mem.alloc(w.partials_bytes);
             first_chunk.push_back(rows.size());
@@ -910,7 +911,7 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
                 }
                 if (int64_t(o) + 1 == ncoup) w.nsrows_coupling = int64_t(srows.size());
             }
-            w.srows = A.mem.upload(srows, stream);
+            w.srows = A.mem.stage(srows, stream);
             w.near_cum = std::move(near_cum);
             A.lists.push_back(w);
         } else {
@@ -922,7 +923,7 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             }
             commit(0, PH_STREAM, sk, A.blocks, std::move(single));
             WorkList &w = A.lists.back();
-            w.srows = A.mem.upload(srows, stream);
+            w.srows = A.mem.stage(srows, stream);
             w.nsrows_coupling = ncoup;
             w.near_cum = std::move(near_cum);
         }
@@ -949,10 +950,10 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
         lb[j] = s.begin[lf + j];
         le[j] = s.end[lf + j];
     }
-    A.d_off_U = A.mem.upload(A.off_U, stream);
-    A.d_off_VT = A.mem.upload(A.off_VT, stream);
-    A.d_off_E = A.mem.upload(A.off_E, stream);
-    A.d_off_FT = A.mem.upload(A.off_FT, stream);
+    A.d_off_U = A.mem.stage(A.off_U, stream);
+    A.d_off_VT = A.mem.stage(A.off_VT, stream);
+    A.d_off_E = A.mem.stage(A.off_E, stream);
+    A.d_off_FT = A.mem.stage(A.off_FT, stream);
     // the sweeps' launches
     A.up_steps.clear();
     A.down_steps.clear();
@@ -983,8 +984,9 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
     } else {
         A.down_steps.push_back({q, 0, 0, true});   // y = y_near
     }
-    A.d_leaf_begin = A.mem.upload(lb, stream);
-    A.d_leaf_end = A.mem.upload(le, stream);
+    A.d_leaf_begin = A.mem.stage(lb, stream);
+    A.d_leaf_end = A.mem.stage(le, stream);
+    A.mem.close_slab(stream);
     check_hip(hipStreamSynchronize(stream), "upload work lists");
 }
 

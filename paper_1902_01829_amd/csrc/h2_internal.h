@@ -43,12 +43,102 @@ inline void check_hip(hipError_t e, const char *where) {
     if (e != hipSuccess) fail(H2_ERR_DEVICE, std::string(where) + ": " + hipGetErrorString(e));
 }
 
+// Device memory of arenas that are gone, for the next ones: a hipFree of a
+// large block takes ~0.3 ms, and up to 10 ms where a program frees often; one
+// that builds, compresses or transposes in a loop asks for the same sizes
+// again (a matrix of 40,000 points transposed after others had come and gone:
+// 4.6 -> 0.8 ms).  Holds at most kLimit bytes in blocks of at least kLeast,
+// and none once the process has no matrix or batch left.  Blocks come here
+// only after a wait for their device, so any stream may use them next.
+struct DevicePool {
+    static constexpr int64_t kLimit = int64_t(1) << 30, kLeast = 64 << 10;
+    struct Block {
+        int device;
+        int64_t bytes;
+        void *p;
+    };
+    std::mutex m;
+    std::vector<Block> blocks;
+    int64_t held = 0;
+    int live = 0;   // matrices and batches
+
+    static DevicePool &get() {
+        static DevicePool *pool = new DevicePool;   // never destroyed: the HIP runtime may be gone first
+        return *pool;
+    }
+    // A block of nbytes to nbytes * 5/4 (its size in got), or null.
+    void *take(int device, int64_t nbytes, int64_t &got) {
+        std::lock_guard<std::mutex> g(m);
+        size_t best = blocks.size();
+        for (size_t i = 0; i < blocks.size(); ++i)
+            if (blocks[i].device == device && blocks[i].bytes >= nbytes && blocks[i].bytes <= nbytes + nbytes / 4 &&
+                (best == blocks.size() || blocks[i].bytes < blocks[best].bytes))
+                best = i;
+        if (best == blocks.size()) return nullptr;
+        void *p = blocks[best].p;
+        got = blocks[best].bytes;
+        held -= got;
+        blocks.erase(blocks.begin() + long(best));
+        return p;
+    }
+    // False: not kept, the caller frees it.
+    bool give(int device, int64_t nbytes, void *p) {
+        std::lock_guard<std::mutex> g(m);
+        if (live == 0 || nbytes < kLeast || held + nbytes > kLimit) return false;
+        try {
+            blocks.push_back({device, nbytes, p});
+        } catch (const std::bad_alloc &) {
+            return false;
+        }
+        held += nbytes;
+        return true;
+    }
+    void clear() {
+        std::vector<Block> old;
+        {
+            std::lock_guard<std::mutex> g(m);
+            old.swap(blocks);
+            held = 0;
+        }
+        for (const Block &b : old) (void)hipFree(b.p);
+    }
+    void enter() {
+        std::lock_guard<std::mutex> g(m);
+        ++live;
+    }
+    void leave() {
+        bool last;
+        {
+            std::lock_guard<std::mutex> g(m);
+            last = --live == 0;
+        }
+        if (last) clear();
+    }
+};
+
+// Counts its owner among the pool's users; to be declared before (destroyed
+// after) the owner's arenas.
+struct PoolUser {
+    PoolUser() { DevicePool::get().enter(); }
+    ~PoolUser() { DevicePool::get().leave(); }
+    PoolUser(const PoolUser &) = delete;
+    PoolUser &operator=(const PoolUser &) = delete;
+};
+
 // Device allocations of one owner; a test-only cap (environment variable
 // H2MV_DEVICE_BYTE_CAP, bytes) turns any allocation past it into H2_ERR_OOM.
 struct DeviceArena {
-    std::vector<void *> ptrs;
+    std::vector<DevicePool::Block> ptrs;
     int64_t bytes = 0;
     int64_t cap = -1;
+    // Small set-up arrays are placed in slabs and copied a slab at a time: an
+    // array of its own costs an allocation, a copy and a wait, ~40 us, and a
+    // matrix has about a hundred of them (one of 40,000 points transposed:
+    // 2.8 -> 1.2 ms).
+    static constexpr int64_t kSlab = 1 << 20, kSlabItem = 256 << 10;
+    char *slab = nullptr;
+    int64_t slab_used = 0, slab_sent = 0;   // bytes placed, and of these copied
+    std::vector<char> slab_host;
 
     DeviceArena() {
         if (const char *c = std::getenv("H2MV_DEVICE_BYTE_CAP")) cap = std::atoll(c);
@@ -56,31 +146,67 @@ struct DeviceArena {
     DeviceArena(const DeviceArena &) = delete;
     DeviceArena &operator=(const DeviceArena &) = delete;
     ~DeviceArena() {
-        for (void *p : ptrs) (void)hipFree(p);
+        release();
     }
     void swap(DeviceArena &o) {
         std::swap(ptrs, o.ptrs);
         std::swap(bytes, o.bytes);
         std::swap(cap, o.cap);
+        std::swap(slab, o.slab);
+        std::swap(slab_used, o.slab_used);
+        std::swap(slab_sent, o.slab_sent);
+        std::swap(slab_host, o.slab_host);
     }
     void *alloc(int64_t nbytes) {
         if (nbytes <= 0) nbytes = 16;
         nbytes = (nbytes + 255) / 256 * 256;
         if (cap >= 0 && bytes + nbytes > cap) fail(H2_ERR_OOM, "device byte cap exceeded");
-        void *p = nullptr;
+        void *p = device_malloc(nbytes);
+        bytes += nbytes;
+        return p;
+    }
+    void *device_malloc(int64_t nbytes) {   // not counted
+        int device = 0;
+        check_hip(hipGetDevice(&device), "hipGetDevice");
+        int64_t got = nbytes;
+        ptrs.reserve(ptrs.size() + 1);
+        void *p = nbytes >= DevicePool::kLeast ? DevicePool::get().take(device, nbytes, got) : nullptr;
+        if (p) {
+            ptrs.push_back({device, got, p});
+            return p;
+        }
         hipError_t e = hipMalloc(&p, size_t(nbytes));
+        if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {   // again without what the pool holds
+            (void)hipGetLastError();
+            DevicePool::get().clear();
+            e = hipMalloc(&p, size_t(nbytes));
+        }
         if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
             (void)hipGetLastError();
             fail(H2_ERR_OOM, "hipMalloc of " + std::to_string(nbytes) + " bytes failed");
         }
         check_hip(e, "hipMalloc");
-        ptrs.push_back(p);
-        bytes += nbytes;
+        ptrs.push_back({device, nbytes, p});
         return p;
     }
-    template <typename T>
+    // Returns the memory: the smallest block to the device, and after that,
+    // as hipFree waits for all work on its device, the others to the pool.
+    void release() {
+        if (ptrs.empty()) return;
+        std::swap(*std::min_element(ptrs.begin(), ptrs.end(),
+                                    [](const DevicePool::Block &x, const DevicePool::Block &y) { return x.bytes < y.bytes; }),
+                  ptrs.front());
+        const bool idle = hipFree(ptrs.front().p) == hipSuccess;
+        for (size_t i = 1; i < ptrs.size(); ++i) {
+            const DevicePool::Block &b = ptrs[i];
+            if (!idle || b.device != ptrs.front().device || !DevicePool::get().give(b.device, b.bytes, b.p))
+                (void)hipFree(b.p);
+        }
+        ptrs.clear();
+    }
     // Copies v to new device memory; returns once v may be released (set-up
     // only, never inside a product).
+    template <typename T>
     T *upload(const std::vector<T> &v, hipStream_t st) {
         T *d = static_cast<T *>(alloc(int64_t(v.size() * sizeof(T))));
         if (!v.empty()) {
@@ -89,6 +215,41 @@ struct DeviceArena {
             check_hip(hipStreamSynchronize(st), "upload");
         }
         return d;
+    }
+    // The same, but a small v arrives on the device with the next flush().
+    // Counted as an allocation of its own.
+    template <typename T>
+    T *stage(const std::vector<T> &v, hipStream_t st) {
+        const int64_t nbytes = std::max<int64_t>(16, int64_t(v.size() * sizeof(T))), place = (nbytes + 255) / 256 * 256;
+        if (place > kSlabItem) return upload(v, st);
+        if (cap >= 0 && bytes + place > cap) fail(H2_ERR_OOM, "device byte cap exceeded");
+        if (!slab || slab_used + place > kSlab) {
+            flush(st);
+            slab = static_cast<char *>(device_malloc(kSlab));
+            slab_used = slab_sent = 0;
+            slab_host.resize(size_t(kSlab));
+        }
+        T *d = reinterpret_cast<T *>(slab + slab_used);
+        if (!v.empty()) std::memcpy(slab_host.data() + slab_used, v.data(), v.size() * sizeof(T));
+        slab_used += place;
+        bytes += place;
+        return d;
+    }
+    // Everything staged is on the device; no more is needed of the host's copy.
+    void flush(hipStream_t st) {
+        if (slab_used > slab_sent) {
+            check_hip(hipMemcpyAsync(slab + slab_sent, slab_host.data() + slab_sent, size_t(slab_used - slab_sent),
+                                     hipMemcpyHostToDevice, st),
+                      "hipMemcpyAsync");
+            check_hip(hipStreamSynchronize(st), "upload");
+            slab_sent = slab_used;
+        }
+    }
+    // Nothing more will be staged.
+    void close_slab(hipStream_t st) {
+        flush(st);
+        slab = nullptr;
+        std::vector<char>().swap(slab_host);
     }
 };
 
@@ -168,6 +329,7 @@ struct BatchSlot {
 
 // The matrix behind an h2_handle: its structure, device storage and work lists.
 struct h2_matrix_ {
+    h2i::PoolUser pool_user;
     h2::Structure st;
     int storage = H2_FP64;
     bool structure_only = false;
@@ -234,6 +396,7 @@ struct h2_matrix_ {
 
 // A batch of matrices behind an h2_batch: one launch per level slot.
 struct h2_batch_ {
+    h2i::PoolUser pool_user;
     std::vector<h2_matrix_ *> mats;
     int nrhs = 0;
     h2i::DeviceArena mem;
