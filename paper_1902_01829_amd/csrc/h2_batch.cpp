@@ -74,22 +74,26 @@ void store_config(const std::string &sig, const h2::MmConfig &cfg) {
     }
 }
 
-// Launch shapes the tuners try: the block loop's prefetch depth (0 plain, 1
-// the next block, 2 and 3 rings of block slots in registers, 4 and 5 rings
-// with a row's halves sharing the input tile (32-wide tiles), 6 and 7 rings
-// of 6 or 8 column chunks (16-wide tiles)), and for passes of at most 16
-// right-hand sides the MFMA tile width (16: 16x16 MFMAs, half the matrix-core
-// work and registers of 32, but every tile pads 8 right-hand sides to 16;
-// 32: 32x32 MFMAs).  Depth 3 with 32-wide tiles runs one wavefront per SIMD.
-constexpr int kDepths = h2::MM_MAX_PIPE + 1;   // each with the tile widths h2::mm_pipe_fits allows
-
-std::vector<int> tile_widths(int ncols) {
-    return ncols <= 16 ? std::vector<int>{16, 32} : std::vector<int>{32};
+// Launch shapes the tuners try.  Passes of more than 16 right-hand sides: the
+// block loop's prefetch depth (0 plain, 1 the next block, 2 and 3 rings of
+// block slots in registers, 4 and 5 rings with a row's halves sharing the
+// input tile) with several grids.  Passes of at most 16 run the streaming
+// launch one way, so that only the sweeps' depth is left to choose: 16-wide
+// tiles, plain, a ring of 2 blocks or of 6 column chunks, one workgroup per 4
+// items (the other depths, persistent grids and 32-wide tiles were never the
+// fastest by more than 1 % with this streaming launch; the first product of a
+// batch of 24 took 183 ms with all of them, 8.6 ms with these, that of a 3-D
+// matrix of 50,021 points 59 and 2.9 ms).
+std::vector<h2::MmConfig> tile_candidates(int ncols, std::initializer_list<int64_t> grids) {
+    if (ncols <= 16) return {{0, 0, 16}, {2, 0, 16}, {6, 0, 16}};
+    std::vector<h2::MmConfig> c;
+    for (int pipe = 0; pipe < h2::MM_FIRST_CRING; ++pipe)
+        for (int64_t grid : grids) c.push_back({pipe, grid, 32});
+    return c;
 }
 
 // Times every candidate configuration on the batch (tables set) and keeps the
-// fastest: prefetch depth x tile width x grid (persistent grids of 1, 2 and 4
-// workgroups per compute unit, or one workgroup per two rows).
+// fastest (persistent grids: 1, 2 and 4 workgroups per compute unit).
 void batch_autotune(h2_batch_ &B) {
     h2::MmConfig best{1, 0, 0};
     if (cached_config(B.signature, best)) {
@@ -102,28 +106,23 @@ void batch_autotune(h2_batch_ &B) {
     check_hip(hipEventCreate(&t1), "hipEventCreate");
     double best_ms = 1e30;
     const int64_t cu = (B.cu_count + h2::MM_XCDS - 1) / h2::MM_XCDS * h2::MM_XCDS;
-    const int64_t grids[4] = {0, cu, 2 * cu, 4 * cu};
-    for (int nt : tile_widths(B.nrhs))
-        for (int pipe = 0; pipe < kDepths; ++pipe)
-            for (int64_t grid : grids) {
-                if (!h2::mm_pipe_fits(pipe, nt)) continue;
-                const h2::MmConfig c{pipe, grid, nt};
-                batch_enqueue(B, c, B.own);   // warm-up
-                float ms_best = 1e30f;
-                for (int rep = 0; rep < 2; ++rep) {
-                    check_hip(hipEventRecord(t0, B.own), "hipEventRecord");
-                    batch_enqueue(B, c, B.own);
-                    check_hip(hipEventRecord(t1, B.own), "hipEventRecord");
-                    check_hip(hipEventSynchronize(t1), "hipEventSynchronize");
-                    float ms = 0.0f;
-                    check_hip(hipEventElapsedTime(&ms, t0, t1), "hipEventElapsedTime");
-                    ms_best = std::min(ms_best, ms);
-                }
-                if (ms_best < best_ms) {
-                    best_ms = ms_best;
-                    best = c;
-                }
-            }
+    for (const h2::MmConfig &c : tile_candidates(B.nrhs, {0, cu, 2 * cu, 4 * cu})) {
+        batch_enqueue(B, c, B.own);   // warm-up
+        float ms_best = 1e30f;
+        for (int rep = 0; rep < 2; ++rep) {
+            check_hip(hipEventRecord(t0, B.own), "hipEventRecord");
+            batch_enqueue(B, c, B.own);
+            check_hip(hipEventRecord(t1, B.own), "hipEventRecord");
+            check_hip(hipEventSynchronize(t1), "hipEventSynchronize");
+            float ms = 0.0f;
+            check_hip(hipEventElapsedTime(&ms, t0, t1), "hipEventElapsedTime");
+            ms_best = std::min(ms_best, ms);
+        }
+        if (ms_best < best_ms) {
+            best_ms = ms_best;
+            best = c;
+        }
+    }
     (void)hipEventDestroy(t0);
     (void)hipEventDestroy(t1);
     B.cfg = best;
@@ -310,23 +309,19 @@ void tune_tiles(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t 
         check_hip(hipGetDevice(&dev), "hipGetDevice");
         check_hip(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device attribute");
         const int64_t cu = (cus + h2::MM_XCDS - 1) / h2::MM_XCDS * h2::MM_XCDS;
-        for (int nt : tile_widths(ncols))
-            for (int pipe = 0; pipe < kDepths; ++pipe)
-                for (int64_t grid : {int64_t(0), cu, 2 * cu}) {
-                    if (!h2::mm_pipe_fits(pipe, nt)) continue;
-                    const h2::MmConfig c{pipe, grid, nt};
-                    run_tile_pass(A, X, ldx, Y, ldy, nrhs, j0, c, st);   // warm-up
-                    check_hip(hipEventRecord(t0, st), "hipEventRecord");
-                    run_tile_pass(A, X, ldx, Y, ldy, nrhs, j0, c, st);
-                    check_hip(hipEventRecord(t1, st), "hipEventRecord");
-                    check_hip(hipEventSynchronize(t1), "hipEventSynchronize");
-                    float ms = 0.0f;
-                    check_hip(hipEventElapsedTime(&ms, t0, t1), "hipEventElapsedTime");
-                    if (ms < bms) {
-                        bms = ms;
-                        best = c;
-                    }
-                }
+        for (const h2::MmConfig &c : tile_candidates(ncols, {0, cu, 2 * cu})) {
+            run_tile_pass(A, X, ldx, Y, ldy, nrhs, j0, c, st);   // warm-up
+            check_hip(hipEventRecord(t0, st), "hipEventRecord");
+            run_tile_pass(A, X, ldx, Y, ldy, nrhs, j0, c, st);
+            check_hip(hipEventRecord(t1, st), "hipEventRecord");
+            check_hip(hipEventSynchronize(t1), "hipEventSynchronize");
+            float ms = 0.0f;
+            check_hip(hipEventElapsedTime(&ms, t0, t1), "hipEventElapsedTime");
+            if (ms < bms) {
+                bms = ms;
+                best = c;
+            }
+        }
         (void)hipEventDestroy(t0);
         (void)hipEventDestroy(t1);
         A.prof = prof;

@@ -1348,6 +1348,8 @@ H2_MM_PHASE_KERNEL(mm_downsweep_kernel, false)
 H2_MM_PHASE_KERNEL(mm_leafexpand_kernel, true)
 #undef H2_MM_PHASE_KERNEL
 
+#include "h2_mm16.h"
+
 // Copies right-hand sides j0 .. j0+NT-1 of the caller's column-major FP64 X
 // into point tiles: leaf j at j * slot, [rhs][row] with a leading dimension of
 // its size rounded up to 16, zero-padded (rows and missing right-hand sides).
@@ -1397,11 +1399,13 @@ static void launch_phase_nt(const MmArgs &g, int kind, int phase, unsigned grid,
     case PHASE_LEAF:
         hipLaunchKernelGGL((mm_leafexpand_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
         break;
-    default:
-        if (kind == ELEM_F32)
-            hipLaunchKernelGGL((mm_stream_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
-        else
-            hipLaunchKernelGGL((mm_stream_kernel<ELEM_BF16, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
+    default:   // (16-wide: launch_narrow)
+        if constexpr (NT == 32) {
+            if (kind == ELEM_F32)
+                hipLaunchKernelGGL((mm_stream_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
+            else
+                hipLaunchKernelGGL((mm_stream_kernel<ELEM_BF16, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
+        }
     }
 }
 
@@ -1429,18 +1433,29 @@ static void launch_phase(const MmArgs &g, int kind, int phase, int nt, int depth
     }
 }
 
+// The streaming launch of a pass of at most 16 right-hand sides.
+template <bool BATCH>
+static void launch_narrow(const MmArgs &g, int kind, const int32_t *pitems, int64_t npitems, hipStream_t st) {
+    const dim3 grid(unsigned(npitems / 2)), block(64 * kNarrowWaves);
+    if (kind == ELEM_F32)
+        hipLaunchKernelGGL((mm_stream_narrow_kernel<ELEM_F32, BATCH>), grid, block, 0, st, g, g.rows, g.blks, pitems, g.scales);
+    else
+        hipLaunchKernelGGL((mm_stream_narrow_kernel<ELEM_BF16, BATCH>), grid, block, 0, st, g, g.rows, g.blks, pitems, g.scales);
+}
+
 hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg, hipStream_t st) {
     if (L.nitems <= 0) return hipSuccess;
     if (L.nitems % (4 * MM_XCDS) != 0) return hipErrorInvalidValue;
     if (phase != PHASE_STREAM && kind != ELEM_F32) return hipErrorInvalidValue;   // bases are FP32
     if (L.ncols < 1 || L.ncols > MM_TILE) return hipErrorInvalidValue;
     const bool pair = cfg.pipelined >= MM_FIRST_PAIR && cfg.pipelined < MM_FIRST_CRING;
-    if (pair && (L.npitems <= 0 || L.npitems % (2 * MM_XCDS) != 0)) return hipErrorInvalidValue;
+    if ((pair || phase == PHASE_STREAM) && (L.npitems <= 0 || L.npitems % (2 * MM_XCDS) != 0)) return hipErrorInvalidValue;
     MmArgs g{L.rows, pair ? L.pitems : L.items, pair ? L.npitems : L.nitems, L.blks, L.data, L.scales, L.in_tree,
              L.in_pts, L.init, L.out_tree, L.out_pts, L.Y, L.ldy, nullptr, nullptr, L.ncols};
     const int nt = cfg.nt == 32 || L.ncols > 16 ? 32 : 16;
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
-    if (cfg.grid > 0 && cfg.grid < slots) launch_phase<false, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
+    if (phase == PHASE_STREAM && nt == 16) launch_narrow<false>(g, kind, L.pitems, L.npitems, st);
+    else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<false, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
     else launch_phase<false, false>(g, kind, phase, nt, cfg.pipelined, unsigned(slots), st);
     return hipGetLastError();
 }
@@ -1450,13 +1465,14 @@ hipError_t launch_mm_batch(const MmBatchLaunch &L, int kind, int phase, const Mm
     if (L.nitems % (4 * MM_XCDS) != 0) return hipErrorInvalidValue;
     if (phase != PHASE_STREAM && kind != ELEM_F32) return hipErrorInvalidValue;
     const bool pair = cfg.pipelined >= MM_FIRST_PAIR && cfg.pipelined < MM_FIRST_CRING;
-    if (pair && (L.npitems <= 0 || L.npitems % (2 * MM_XCDS) != 0)) return hipErrorInvalidValue;
+    if ((pair || phase == PHASE_STREAM) && (L.npitems <= 0 || L.npitems % (2 * MM_XCDS) != 0)) return hipErrorInvalidValue;
     MmArgs g{L.rows, pair ? L.pitems : L.items, pair ? L.npitems : L.nitems, L.blks, nullptr, L.scales, L.pool,
              L.pool, L.pool, L.pool, L.pool, nullptr, 0, L.Ytab, L.ldytab, L.ncols};
     if (L.ncols < 1 || L.ncols > MM_TILE) return hipErrorInvalidValue;
     const int nt = cfg.nt == 32 || L.ncols > 16 ? 32 : 16;
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
-    if (cfg.grid > 0 && cfg.grid < slots) launch_phase<true, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
+    if (phase == PHASE_STREAM && nt == 16) launch_narrow<true>(g, kind, L.pitems, L.npitems, st);
+    else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<true, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
     else launch_phase<true, false>(g, kind, phase, nt, cfg.pipelined, unsigned(slots), st);
     return hipGetLastError();
 }

@@ -1,0 +1,227 @@
+// The streaming launch for at most 16 right-hand sides, FP32 and BF16 blocks.
+// Included at the end of h2_mm.hip's namespace.
+//
+// One workgroup of four wavefronts takes a unit of the pair list: a row of
+// more than 32 rows, a quarter of its blocks per wavefront, or two shorter
+// rows, half of a row's blocks per wavefront.  A wavefront multiplies whole
+// blocks (up to 64 rows): the input tile is read, and for BF16 blocks split,
+// once per block and not once per 32-row half, and the long rows of 3-D
+// matrices are spread over four wavefronts.  The FP64 totals are added
+// through LDS in a fixed order.
+//
+// Within a wavefront the row's blocks are one sequence of 16-column chunks
+// (BF16: 32), in a ring of S slots with loads in flight across block
+// boundaries.  What a step costs beyond its loads and MFMAs bounds this
+// kernel for blocks of rank 16 to 27, so it is kept small: block addresses
+// stay in scalar registers (descriptors of 64 blocks are loaded at a time, one
+// per lane, and read with lane reads), a lane's offset within a chunk is one
+// multiplication, and what consuming a chunk needs to know of its block (its
+// last chunk, its scale) is kept with the ring slot.  A block's products and
+// their order are those of the other loops.
+// 8 right-hand sides, streaming launch, before (best of the 32-row loops) and
+// now: 2-D 400,000 points FP32 1.78 -> 1.63 ms (4.8 TB/s of block bytes), 3-D
+// 50,021 points of rank 27 BF16 402 -> 317 us; whole products of 4,096 points
+// 63 -> 50 us, of a batch of 24 at FP32 975 -> 840 us.  Insensitive to S (2 to
+// 10) and to two to four wavefronts per SIMD; the L1 caches' address
+// processing is busy 82 % of the time (256-byte runs that start anywhere, for
+// the blocks; 64-byte ones for the tiles: reading a fixed 1 KiB instead of
+// them gains 5 to 14 %).
+
+constexpr int kNarrowWaves = 4;
+
+// Rows of a wavefront: NH tiles of 16.
+template <int KIND, int NH> struct NarrowSlot {
+    typename std::conditional<KIND == ELEM_F32, f32x4, u32x4>::type a[NH];
+    f32x4 b[KIND == ELEM_F32 ? 1 : 2];
+};
+
+template <int KIND, bool BATCH, int NH, int S>
+__device__ __forceinline__ void narrow_blocks(const MmArgs &g, const RowDesc &rd, int first, int cnt, int lane,
+                                              double (&tot)[NH][4]) {
+    constexpr int CH = KIND == ELEM_F32 ? 16 : 32;   // columns of a chunk
+    constexpr int W = KIND == ELEM_F32 ? 4 : 8;      // columns of a 16-byte item
+    const int n = lane & 15, kq = lane >> 4, R = rd.R, nh = (R + 15) >> 4;
+    const uint32_t R16 = uint32_t(R) * 16;
+    uint32_t ro[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) ro[h] = uint32_t(16 * h + n < R ? 16 * h + n : R - 1) * 16;
+    const char *xbase = reinterpret_cast<const char *>((rd.sel & ROW_IN_X) ? g.in_pts : g.in_tree);
+    const BlkDesc *blks = g.blks + first;
+
+    // descriptors of blocks 64 j .. 64 j + 63 (of the last block past the end), one per lane
+    BlkDesc my;
+    float mysc = 1.0f;
+    auto load_descs = [&](int k0) {
+        my = blks[k0 + lane < cnt ? k0 + lane : cnt - 1];
+        if constexpr (KIND == ELEM_BF16) mysc = g.scales[my.sidx];
+        asm volatile("" : "+v"(my.C), "+v"(mysc));   // waited for here, not at every later use of a load
+    };
+    int total = 0;   // chunks
+    for (int k0 = cnt > 64 ? 64 : 0;;) {   // (the first 64 last: they stay)
+        load_descs(k0);
+        const int C = k0 + lane < cnt ? my.C : 0;
+#pragma unroll
+        for (int t = 0; t < 64; t += CH) total += __popcll(__ballot(C > t));
+        if (k0 == 0) break;
+        k0 = k0 + 64 < cnt ? k0 + 64 : 0;
+    }
+    // refill cursor: chunk c of block k
+    int k = 0, c = 0, C = 0, np = 0;
+    const char *ap = nullptr, *xp = nullptr;
+    auto open = [&] {
+        const int j = k & 63;
+        const int64_t a = readlane64(my.a, j);
+        if constexpr (BATCH) ap = reinterpret_cast<const char *>(a);
+        else ap = static_cast<const char *>(g.data) + a * (KIND == ELEM_F32 ? 4 : 2);
+        xp = xbase + readlane64(my.in, j) * 4;
+        C = __builtin_amdgcn_readlane(my.C, j);
+        np = (C + CH - 1) / CH;
+    };
+    open();
+    NarrowSlot<KIND, NH> ring[S];
+    bool last[S];
+    float sc[S];
+    int rem[S];   // BF16: padded columns of the tile from the chunk's first on
+    auto refill = [&](int s) {
+        const uint32_t live = k < cnt ? ~0u : 0u;   // past the end: one item of the last block, unused
+        const int groups = (C + W - 1) / W - (CH / W) * c;   // item columns from this chunk on
+        const uint32_t ko = uint32_t(kq < groups ? kq : groups - 1) * R16;
+        const int Cp = round16(C);
+        typedef const __attribute__((address_space(1))) char *gptr;
+        typedef typename std::conditional<KIND == ELEM_F32, f32x4, u32x4>::type item;
+#pragma unroll
+        for (int h = 0; h < NH; ++h)
+            ring[s].a[h] = __builtin_nontemporal_load(
+                reinterpret_cast<const __attribute__((address_space(1))) item *>((gptr)ap + ((ko + ro[h]) & live)));
+        last[s] = c + 1 == np;
+        if constexpr (KIND == ELEM_F32) {
+            const uint32_t xo = uint32_t(n * Cp) * 4 + uint32_t(kq) * 16;
+            ring[s].b[0] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo);
+        } else {
+            rem[s] = Cp - CH * c;
+            const int col = 8 * kq < rem[s] ? 8 * kq : rem[s] - 8;
+            const uint32_t xo = uint32_t(n * Cp + col) * 4;
+            ring[s].b[0] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo);
+            ring[s].b[1] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo + 16);
+            sc[s] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mysc), k & 63));
+        }
+        if (live) {
+            if (++c < np) {
+                ap += (CH / W) * R16;
+                xp += CH * 4;
+            } else if (++k < cnt) {
+                if ((k & 63) == 0) load_descs(k);
+                c = 0;
+                open();
+            } else {
+                --c;   // the cursor stays on the last chunk
+            }
+        }
+    };
+    f32x4 acc[NH];
+#pragma unroll
+    for (int h = 0; h < NH; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    auto consume = [&](int s) {
+        if constexpr (KIND == ELEM_F32) {
+            const f32x4 b = ring[s].b[0];
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                if (h >= nh) break;   // wave-uniform
+                const f32x4 a = ring[s].a[h];
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc[h], 0, 0, 0);
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc[h], 0, 0, 0);
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc[h], 0, 0, 0);
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc[h], 0, 0, 0);
+            }
+        } else {
+            bf16x8 hi, mid, lo;
+            split3(ring[s].b[0], ring[s].b[1], hi, mid, lo);
+            if (8 * kq >= rem[s]) {   // past the tile: zero
+                const u32x4 z = {0u, 0u, 0u, 0u};
+                hi = mid = lo = __builtin_bit_cast(bf16x8, z);
+            }
+#pragma unroll
+            for (int h = 0; h < NH; ++h) {
+                if (h >= nh) break;
+                const bf16x8 a = __builtin_bit_cast(bf16x8, ring[s].a[h]);
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo, acc[h], 0, 0, 0);
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, mid, acc[h], 0, 0, 0);
+                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi, acc[h], 0, 0, 0);
+            }
+        }
+        if (last[s]) {   // the block's sum goes to the totals
+            const double f = KIND == ELEM_F32 ? 1.0 : double(sc[s]);
+#pragma unroll
+            for (int h = 0; h < NH; ++h)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    tot[h][e] += f * double(acc[h][e]);
+                    acc[h][e] = 0.0f;
+                }
+        }
+    };
+#pragma unroll
+    for (int s = 0; s < S; ++s) refill(s);
+    // whole rounds with refills, then the last round (1 .. S chunks) without
+    int i = 0;
+    for (; i + S < total; i += S) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            consume(s);
+            refill(s);
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        if (i + s < total) consume(s);   // wave-uniform
+}
+
+template <int KIND, bool BATCH>
+__global__ __launch_bounds__(64 * kNarrowWaves) void mm_stream_narrow_kernel(MmArgs g, const RowDesc *__restrict__ rows,
+                                                                             const BlkDesc *__restrict__ blks,
+                                                                             const int32_t *__restrict__ items,
+                                                                             const float *__restrict__ scales) {
+    __shared__ double part[kNarrowWaves][16][64];   // [wavefront][tile and element][lane]
+    g.rows = rows;
+    g.blks = blks;
+    g.items = items;
+    g.scales = scales;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int32_t it0 = items[int64_t(blockIdx.x) * 2], it1 = items[int64_t(blockIdx.x) * 2 + 1];
+    if (it0 < 0) return;   // padding of the list (then it1 is padding too)
+    const bool wide = it1 >= 0 && (it0 >> 1) == (it1 >> 1);
+    const int32_t it = wide || wv < 2 ? it0 : it1;
+    RowDesc rd;
+    if (it >= 0) {
+        rd = rows[it >> 1];
+        const int nb = rd.b1 - rd.b0;
+        const int of = wide ? 4 : 2, me = wide ? wv : wv & 1;
+        const int b0 = nb * me / of, cnt = nb * (me + 1) / of - b0;
+        if (wide) {
+            double tot[4][4] = {};
+            if (cnt > 0) narrow_blocks<KIND, BATCH, 4, KIND == ELEM_F32 ? 4 : 2>(g, rd, rd.b0 + b0, cnt, lane, tot);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) part[wv][e][lane] = tot[e >> 2][e & 3];
+        } else {
+            double tot[2][4] = {};
+            if (cnt > 0) narrow_blocks<KIND, BATCH, 2, KIND == ELEM_F32 ? 6 : 4>(g, rd, rd.b0 + b0, cnt, lane, tot);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) part[wv][e][lane] = tot[e >> 2][e & 3];
+        }
+    }
+    __syncthreads();
+    if (it < 0) return;
+    // row tile h of the unit's row by this wavefront
+    const int h = wide ? wv : wv & 1, w0 = wide ? 0 : wv & 2, w1 = wide ? 4 : w0 + 2;
+    const int n = lane & 15, kq = lane >> 4, R = rd.R, Rp = round16(R), i0 = 16 * h + 4 * kq;
+    if (i0 >= Rp) return;
+    double v[4] = {};
+    for (int w = w0; w < w1; ++w)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] += part[w][4 * h + e][lane];
+    f32x4 o;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = i0 + e < R ? float(v[e]) : 0.0f;
+    float *out = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + int64_t(n) * Rp + i0;
+    *reinterpret_cast<f32x4 *>(out) = o;
+}
