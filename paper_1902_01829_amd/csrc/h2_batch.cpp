@@ -17,7 +17,7 @@ BatchConfigCache &config_cache() {
 
 // Enqueues one batched product (tables already set) with configuration cfg.
 void batch_enqueue(h2_batch_ &B, const h2::MmConfig &cfg, hipStream_t st) {
-    check_hip(h2::launch_batch_pack(B.pack, B.npack, B.d_Xtab, B.d_ldx, B.nrhs, B.pool,
+    check_hip(h2::launch_batch_pack(B.pack, B.npack, B.d_Xtab, B.d_ldx, B.nrhs, h2::mm_tile_width(cfg, B.nrhs), B.pool,
                                     cfg.grid > 0 ? cfg.grid : 0, st),
               "batch pack");
     for (const BatchSlot &sl : B.slots) {

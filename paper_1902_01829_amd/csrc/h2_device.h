@@ -219,6 +219,8 @@ struct MmConfig {
     int64_t grid;
     int nt = 0;
 };
+// Right-hand sides per tile of a pass: the launches of one pass agree on it.
+inline int mm_tile_width(const MmConfig &cfg, int ncols) { return cfg.nt == 32 || ncols > 16 ? 32 : 16; }
 hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg, hipStream_t st);
 
 // ---- many right-hand sides, FP64 matrices (h2_mm64.hip)
@@ -268,10 +270,11 @@ struct PackEntry {
     int32_t member;
 };
 hipError_t launch_batch_pack(const PackEntry *entries, int64_t count, double const *const *Xtab,
-                             const int64_t *ldxtab, int nrhs, float *pool, int64_t grid, hipStream_t st);
-// Packs right-hand sides j0 .. j0+MM_TILE-1 of X (column-major, ldx) into point tiles.
+                             const int64_t *ldxtab, int nrhs, int tile_width, float *pool, int64_t grid, hipStream_t st);
+// Packs right-hand sides j0 .. j0+MM_TILE-1 of X (column-major, ldx) into point tiles (16: j0+15).
 hipError_t launch_pack(const double *X, int64_t ldx, int j0, int nrhs, const int64_t *leaf_begin,
-                       const int64_t *leaf_end, int64_t nleaves, int64_t slot, float *tiles, hipStream_t st);
+                       const int64_t *leaf_end, int64_t nleaves, int64_t slot, float *tiles, int tile_width,
+                       hipStream_t st);
 
 // ---- basis orthogonalization and projection (FP64, symmetric)
 // Doubles allocated after every T array handed to launch_project: the

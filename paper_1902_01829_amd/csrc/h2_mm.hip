@@ -517,134 +517,84 @@ __device__ inline void mm_row_ring(const MmArgs &g, int64_t row, int mt, int lan
     mm_store32<LEAF, BATCH>(g, rd, mt, li, lg, tot);
 }
 
-// ---- 16 right-hand sides (passes of at most 16 columns, batches of <= 16)
-// The tiles keep their layout; only their first 16 right-hand sides are
-// used.  A wavefront still owns a 32-row half of an output segment, as two
-// 16-row MFMA tiles h = 0, 1: lane l owns block row 32*mt + 16*h + (l % 16)
-// and right-hand side l % 16, and lane group q = l / 16 supplies K values.
-// FP32 blocks: v_mfma_f32_16x16x4_f32; per 16 block columns, lane group q
-// loads the 4 columns 16c + 4q .. 16c + 4q + 3 (one 16-byte item) and step t
-// uses column 16c + 4q + t.  BF16 blocks: v_mfma_f32_16x16x32_bf16 with the
-// exact three-way split of the input tile; per 32 block columns lane group q
-// holds columns 32c + 8q .. 32c + 8q + 7 (one 16-byte item).
-template <int KIND> struct BlockA16;
-template <> struct BlockA16<ELEM_F32> {
+// ---- 16 right-hand sides (passes of at most 16 columns, batches of <= 16):
+// the sweeps (FP32 bases); the streaming launch has a loop of its own below.
+// Tiles of these passes hold 16 right-hand sides, four rows of one right-hand
+// side together: row r of right-hand side n at ((r / 4) * 16 + n) * 4 + r % 4,
+// so that the 16-byte values of a wavefront (lane l: right-hand side l % 16,
+// rows 4 (l / 16) .. + 3 of 16) are one run of 1 KiB and not 16 of 64 bytes
+// (8 right-hand sides, FP32: batch of 24 847 -> 783 us, 2-D 400,000 points
+// 1.99 -> 1.86 ms; 3-D 50,021 points BF16 384 -> 363 us).
+// A wavefront owns a 32-row half of an output segment, as two 16-row MFMA
+// tiles h = 0, 1: lane l owns block row 32*mt + 16*h + (l % 16) and
+// right-hand side l % 16, and lane group q = l / 16 supplies K values:
+// v_mfma_f32_16x16x4_f32; per 16 block columns, lane group q loads the 4
+// columns 16c + 4q .. 16c + 4q + 3 (one 16-byte item) and step t uses column
+// 16c + 4q + t.
+__device__ inline int tile16(int r, int n) { return ((r >> 2) * 16 + n) * 4 + (r & 3); }
+
+struct BlockA16 {
     f32x4 v[2][4];   // [row tile][16-column chunk]
 };
-template <> struct BlockA16<ELEM_BF16> {
-    u32x4 v[2][2];   // [row tile][32-column chunk]
-};
 struct TileB16 {
-    f32x4 v[4];      // FP32: one per 16-column chunk; BF16: two per 32-column chunk
+    f32x4 v[4];      // one per 16-column chunk
 };
 
-template <int KIND>
 __device__ inline void load_a16(const BlkDesc &bd, const void *blk, int R, const int (&ic)[2], int nh, int kq,
-                                BlockA16<KIND> &o) {
-    const int C = bd.C;
-    if constexpr (KIND == ELEM_F32) {
-        const int NC = round16(C) >> 4, CW = (C + 3) >> 2;
+                                BlockA16 &o) {
+    const int C = bd.C, NC = round16(C) >> 4, CW = (C + 3) >> 2;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (c >= NC) break;   // wave-uniform
-            const int cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
+    for (int c = 0; c < 4; ++c) {
+        if (c >= NC) break;   // wave-uniform
+        const int cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
 #pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h >= nh) break;
-                o.v[h][c] = load_block_item(reinterpret_cast<const f32x4 *>(
-                    static_cast<const float *>(blk) + (int64_t(cgc) * R + ic[h]) * 4));
-            }
-        }
-    } else {
-        const int NC = (C + 31) >> 5, CW = (C + 7) >> 3;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            if (c >= NC) break;
-            const int cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h >= nh) break;
-                o.v[h][c] = load_block_item(reinterpret_cast<const u32x4 *>(
-                    static_cast<const uint16_t *>(blk) + (int64_t(cgc) * R + ic[h]) * 8));
-            }
+        for (int h = 0; h < 2; ++h) {
+            if (h >= nh) break;
+            o.v[h][c] = load_block_item(
+                reinterpret_cast<const f32x4 *>(static_cast<const float *>(blk) + (int64_t(cgc) * R + ic[h]) * 4));
         }
     }
 }
 
-// Input-tile operand.  BF16 chunks may reach past the tile's padded height
-// (a multiple of 16): such lanes read the chunk's first columns instead and
-// zero them at use.
-template <int KIND>
 __device__ inline void load_b16(const BlkDesc &bd, const float *xbase, int n, int kq, TileB16 &o) {
-    const int Cp = round16(bd.C);
-    const float *xb = xbase + bd.in + n * Cp;
-    if constexpr (KIND == ELEM_F32) {
-        const int NC = Cp >> 4;
+    const int NC = round16(bd.C) >> 4;
+    const float *xb = xbase + bd.in;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (c >= NC) break;
-            o.v[c] = *reinterpret_cast<const f32x4 *>(xb + 16 * c + 4 * kq);
-        }
-    } else {
-        const int NC = (bd.C + 31) >> 5;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            if (c >= NC) break;
-            const int col = 32 * c + 8 * kq, colc = col < Cp ? col : 32 * c;
-            o.v[2 * c] = *reinterpret_cast<const f32x4 *>(xb + colc);
-            o.v[2 * c + 1] = *reinterpret_cast<const f32x4 *>(xb + colc + 4);
-        }
+    for (int c = 0; c < 4; ++c) {
+        if (c >= NC) break;
+        o.v[c] = *reinterpret_cast<const f32x4 *>(xb + tile16(16 * c + 4 * kq, n));
     }
 }
 
-template <int KIND>
-__device__ inline void block_products16(const BlockA16<KIND> &a_op, const TileB16 &b_op, int C, int nh, int kq,
-                                        f32x4 (&acc)[2]) {
+// Products of chunk c accumulated into acc.
+__device__ inline void chunk_products16(const BlockA16 &a_op, const TileB16 &b_op, int c, int nh, f32x4 (&acc)[2]) {
+    const f32x4 b = b_op.v[c];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        if (h >= nh) break;
+        const f32x4 a = a_op.v[h][c];
+        acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc[h], 0, 0, 0);
+        acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc[h], 0, 0, 0);
+        acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc[h], 0, 0, 0);
+        acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc[h], 0, 0, 0);
+    }
+}
+
+__device__ inline void block_products16(const BlockA16 &a_op, const TileB16 &b_op, int C, int nh, f32x4 (&acc)[2]) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-    if constexpr (KIND == ELEM_F32) {
-        const int NC = round16(C) >> 4;
+    const int NC = round16(C) >> 4;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            if (c >= NC) break;
-            const f32x4 b = b_op.v[c];
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h >= nh) break;
-                const f32x4 a = a_op.v[h][c];
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc[h], 0, 0, 0);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc[h], 0, 0, 0);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc[h], 0, 0, 0);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc[h], 0, 0, 0);
-            }
-        }
-    } else {
-        const int NC = (C + 31) >> 5, Cp = round16(C);
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            if (c >= NC) break;
-            bf16x8 hi, mid, lo;
-            split3(b_op.v[2 * c], b_op.v[2 * c + 1], hi, mid, lo);
-            if (32 * c + 8 * kq >= Cp) {   // past the tile: zero (see load_b16)
-                const u32x4 z = {0u, 0u, 0u, 0u};
-                hi = mid = lo = __builtin_bit_cast(bf16x8, z);
-            }
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                if (h >= nh) break;
-                const bf16x8 a = __builtin_bit_cast(bf16x8, a_op.v[h][c]);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo, acc[h], 0, 0, 0);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, mid, acc[h], 0, 0, 0);
-                acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi, acc[h], 0, 0, 0);
-            }
-        }
+    for (int c = 0; c < 4; ++c) {
+        if (c >= NC) break;
+        chunk_products16(a_op, b_op, c, nh, acc);
     }
 }
 
 // One 32-row half (mt) of an output row segment with 16 right-hand sides.
 // Accumulator element e of row tile h holds row 32*mt + 16*h + 4*(l/16) + e
 // of right-hand side l % 16.
-template <int KIND, bool LEAF, bool BATCH, bool PIPE>
+template <bool LEAF, bool BATCH, bool PIPE>
 __device__ inline void mm_row16(const MmArgs &g, int64_t row, int mt, int lane) {
     const RowDesc rd = g.rows[row];
     const int R = rd.R;
@@ -666,30 +616,30 @@ __device__ inline void mm_row16(const MmArgs &g, int64_t row, int mt, int lane) 
 #pragma unroll
         for (int e = 0; e < 4; ++e) tot[h][e] = 0.0;
 
-    BlockA16<KIND> a_cur, a_nxt;
+    BlockA16 a_cur, a_nxt;
     TileB16 b_cur, b_nxt;
     BlkDesc bd_cur, bd_nxt;
     auto block_ptr = [&](const BlkDesc &bd) -> const void * {
         if constexpr (BATCH) return reinterpret_cast<const void *>(bd.a);
-        else return static_cast<const char *>(data) + bd.a * (KIND == ELEM_F32 ? 4 : 2);
+        else return static_cast<const char *>(data) + bd.a * 4;
     };
     const int nb = rd.b1 - rd.b0;
-    LaneDescs<KIND> ld;
+    LaneDescs<ELEM_F32> ld;
     if (nb > 0) {
         ld.load(g, rd, nb, lane);
         bd_cur = ld.get(g, rd, 0);
-        load_a16<KIND>(bd_cur, block_ptr(bd_cur), R, ic, nh, kq, a_cur);
-        load_b16<KIND>(bd_cur, xbase, n, kq, b_cur);
+        load_a16(bd_cur, block_ptr(bd_cur), R, ic, nh, kq, a_cur);
+        load_b16(bd_cur, xbase, n, kq, b_cur);
     }
     for (int k = 0; k < nb; ++k) {
         const bool more = k + 1 < nb;
         if (PIPE && more) {
             bd_nxt = ld.get(g, rd, k + 1);
-            load_a16<KIND>(bd_nxt, block_ptr(bd_nxt), R, ic, nh, kq, a_nxt);
-            load_b16<KIND>(bd_nxt, xbase, n, kq, b_nxt);
+            load_a16(bd_nxt, block_ptr(bd_nxt), R, ic, nh, kq, a_nxt);
+            load_b16(bd_nxt, xbase, n, kq, b_nxt);
         }
         f32x4 acc[2];
-        block_products16<KIND>(a_cur, b_cur, bd_cur.C, nh, kq, acc);
+        block_products16(a_cur, b_cur, bd_cur.C, nh, acc);
         const double sc = ld.scale(g, k, bd_cur);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -705,8 +655,8 @@ __device__ inline void mm_row16(const MmArgs &g, int64_t row, int mt, int lane) 
                 bd_cur = bd_nxt;
             } else {
                 bd_cur = ld.get(g, rd, k + 1);
-                load_a16<KIND>(bd_cur, block_ptr(bd_cur), R, ic, nh, kq, a_cur);
-                load_b16<KIND>(bd_cur, xbase, n, kq, b_cur);
+                load_a16(bd_cur, block_ptr(bd_cur), R, ic, nh, kq, a_cur);
+                load_b16(bd_cur, xbase, n, kq, b_cur);
             }
         }
     }
@@ -714,82 +664,30 @@ __device__ inline void mm_row16(const MmArgs &g, int64_t row, int mt, int lane) 
     mm_store16<LEAF, BATCH>(g, rd, mt, nh, n, kq, tot);
 }
 
-// Chunks of the 16-wide loop: FP32 blocks have 4 (16 columns), BF16 blocks 2
-// (32 columns).
-template <int KIND> constexpr int chunks16() { return KIND == ELEM_F32 ? 4 : 2; }
-template <int KIND> __device__ inline int used_chunks16(int C) {
-    return KIND == ELEM_F32 ? round16(C) >> 4 : (C + 31) >> 5;
-}
+// Chunks (16 columns) of the 16-wide loops.
+constexpr int kChunks16 = 4;
+__device__ inline int used_chunks16(int C) { return round16(C) >> 4; }
 
 // Chunk c of both operands of the 16-wide loop (load_a16 / load_b16 restricted
 // to one chunk), issued unconditionally like load_chunk32: a missing second
 // row tile re-reads the first's rows (clamped), chunks past the width re-read
 // the last column group, and live == false reads the tile's first items (one
 // per row tile, at different addresses, as in load_chunk32).
-template <int KIND>
 __device__ inline void load_chunk16(const BlkDesc &bd, const void *blk, const float *xbase, int R, const int (&ic)[2],
-                                    int n, int kq, int c, bool live, BlockA16<KIND> &a, TileB16 &b) {
+                                    int n, int kq, int c, bool live, BlockA16 &a, TileB16 &b) {
     const int C = bd.C, Cp = round16(C);
-    const float *xb = xbase + bd.in + n * Cp;
-    if constexpr (KIND == ELEM_F32) {
-        const int CW = (C + 3) >> 2, cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
-        const int col = 16 * c + 4 * kq, colc = col < Cp ? col : Cp - 4;
-        const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + colc);
+    const float *xb = xbase + bd.in;
+    const int CW = (C + 3) >> 2, cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
+    const int col = 16 * c + 4 * kq, colc = col < Cp ? col : Cp - 4;
+    const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + tile16(colc, n));
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const f32x4 *ap = live ? reinterpret_cast<const f32x4 *>(static_cast<const float *>(blk) +
-                                                                     (int64_t(cgc) * R + ic[h]) * 4)
-                                   : reinterpret_cast<const f32x4 *>(xbase + bd.in + 4 * h);
-            a.v[h][c] = load_block_item(ap);
-        }
-        b.v[c] = *bp;
-    } else {
-        const int CW = (C + 7) >> 3, cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
-        const int col = 32 * c + 8 * kq, colc = col < Cp ? col : Cp - 8;
-        const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + colc);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const u32x4 *ap = live ? reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(blk) +
-                                                                     (int64_t(cgc) * R + ic[h]) * 8)
-                                   : reinterpret_cast<const u32x4 *>(xbase + bd.in + 4 * h);
-            a.v[h][c] = load_block_item(ap);
-        }
-        b.v[2 * c] = bp[0];
-        b.v[2 * c + 1] = bp[1];
+    for (int h = 0; h < 2; ++h) {
+        const f32x4 *ap = live ? reinterpret_cast<const f32x4 *>(static_cast<const float *>(blk) +
+                                                                 (int64_t(cgc) * R + ic[h]) * 4)
+                               : reinterpret_cast<const f32x4 *>(xb + 4 * h);
+        a.v[h][c] = load_block_item(ap);
     }
-}
-
-// Products of chunk c accumulated into acc (the steps of block_products16).
-template <int KIND>
-__device__ inline void chunk_products16(const BlockA16<KIND> &a_op, const TileB16 &b_op, int c, int Cp, int nh,
-                                        int kq, f32x4 (&acc)[2]) {
-    if constexpr (KIND == ELEM_F32) {
-        const f32x4 b = b_op.v[c];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (h >= nh) break;
-            const f32x4 a = a_op.v[h][c];
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.x, b.x, acc[h], 0, 0, 0);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.y, b.y, acc[h], 0, 0, 0);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.z, b.z, acc[h], 0, 0, 0);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a.w, b.w, acc[h], 0, 0, 0);
-        }
-    } else {
-        bf16x8 hi, mid, lo;
-        split3(b_op.v[2 * c], b_op.v[2 * c + 1], hi, mid, lo);
-        if (32 * c + 8 * kq >= Cp) {   // past the tile: zero (see load_b16)
-            const u32x4 z = {0u, 0u, 0u, 0u};
-            hi = mid = lo = __builtin_bit_cast(bf16x8, z);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            if (h >= nh) break;
-            const bf16x8 a = __builtin_bit_cast(bf16x8, a_op.v[h][c]);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, lo, acc[h], 0, 0, 0);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, mid, acc[h], 0, 0, 0);
-            acc[h] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, hi, acc[h], 0, 0, 0);
-        }
-    }
+    b.v[c] = *bp;
 }
 
 // Epilogue shared by the 16-wide block loops: accumulator element e of row
@@ -815,7 +713,7 @@ __device__ inline void mm_store16(const MmArgs &g, const RowDesc &rd, int mt, in
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const int j = 2 * c + jp, jc = j < g.ncols ? j : g.ncols - 1;
-                yn[c] = g.init[rd.init + int64_t(jc) * Rp + ic];
+                yn[c] = g.init[rd.init + tile16(ic, jc)];
             }
         }
 #pragma unroll
@@ -843,7 +741,7 @@ __device__ inline void mm_store16(const MmArgs &g, const RowDesc &rd, int mt, in
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int i0 = 32 * mt + 16 * h + 4 * kq, i0c = i0 < Rp ? i0 : Rp - 4;
-                t[h] = *reinterpret_cast<const f32x4 *>(g.init + rd.init + int64_t(n) * Rp + i0c);
+                t[h] = *reinterpret_cast<const f32x4 *>(g.init + rd.init + tile16(i0c, n));
             }
         }
 #pragma unroll
@@ -857,14 +755,14 @@ __device__ inline void mm_store16(const MmArgs &g, const RowDesc &rd, int mt, in
             if (rd.init >= 0) {
                 v[0] += t[h].x; v[1] += t[h].y; v[2] += t[h].z; v[3] += t[h].w;
             }
-            float *o = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + int64_t(n) * Rp + i0;
+            float *o = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + tile16(i0, n);
             *reinterpret_cast<f32x4 *>(o) = f32x4{float(v[0]), float(v[1]), float(v[2]), float(v[3])};
         }
     }
 }
 
 // The 16-wide block loop with a ring of D block slots (as mm_row_ring).
-template <int KIND, bool LEAF, bool BATCH, int D>
+template <bool LEAF, bool BATCH, int D>
 __device__ inline void mm_row16_ring(const MmArgs &g, int64_t row, int mt, int lane) {
     const RowDesc rd = g.rows[row];
     const int R = rd.R;
@@ -880,9 +778,9 @@ __device__ inline void mm_row16_ring(const MmArgs &g, int64_t row, int mt, int l
     const float *xbase = (rd.sel & ROW_IN_X) ? g.in_pts : g.in_tree;
     auto block_ptr = [&](const BlkDesc &bd) -> const void * {
         if constexpr (BATCH) return reinterpret_cast<const void *>(bd.a);
-        else return static_cast<const char *>(g.data) + bd.a * (KIND == ELEM_F32 ? 4 : 2);
+        else return static_cast<const char *>(g.data) + bd.a * 4;
     };
-    constexpr int NCH = chunks16<KIND>();
+    constexpr int NCH = kChunks16;
 
     double tot[2][4];
 #pragma unroll
@@ -890,11 +788,11 @@ __device__ inline void mm_row16_ring(const MmArgs &g, int64_t row, int mt, int l
 #pragma unroll
         for (int e = 0; e < 4; ++e) tot[h][e] = 0.0;
 
-    BlockA16<KIND> a[D];
+    BlockA16 a[D];
     TileB16 b[D];
     BlkDesc bd[D];
     const int nb = rd.b1 - rd.b0;
-    LaneDescs<KIND> ld;
+    LaneDescs<ELEM_F32> ld;
     if (nb > 0) {
         ld.load(g, rd, nb, lane);
 #pragma unroll
@@ -903,22 +801,21 @@ __device__ inline void mm_row16_ring(const MmArgs &g, int64_t row, int mt, int l
             bd[s] = ld.get(g, rd, live ? s : 0);
             const void *blk = block_ptr(bd[s]);
 #pragma unroll
-            for (int c = 0; c < NCH; ++c) load_chunk16<KIND>(bd[s], blk, xbase, R, ic, n, kq, c, live, a[s], b[s]);
+            for (int c = 0; c < NCH; ++c) load_chunk16(bd[s], blk, xbase, R, ic, n, kq, c, live, a[s], b[s]);
         }
     }
     auto step = [&](const int s, const int k) {
         const bool refill = k + D < nb;
         const BlkDesc nx = ld.get(g, rd, refill ? k + D : k);
-        const int np = used_chunks16<KIND>(bd[s].C);
-        const int Cp = round16(bd[s].C);
+        const int np = used_chunks16(bd[s].C);
         const void *nblk = block_ptr(nx);
         f32x4 acc[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            if (c < np) chunk_products16<KIND>(a[s], b[s], c, Cp, nh, kq, acc);
-            load_chunk16<KIND>(nx, nblk, xbase, R, ic, n, kq, c, refill, a[s], b[s]);
+            if (c < np) chunk_products16(a[s], b[s], c, nh, acc);
+            load_chunk16(nx, nblk, xbase, R, ic, n, kq, c, refill, a[s], b[s]);
         }
         const double sc = ld.scale(g, k, bd[s]);
 #pragma unroll
@@ -943,51 +840,37 @@ __device__ inline void mm_row16_ring(const MmArgs &g, int64_t row, int mt, int l
 }
 
 // ---- 16-wide loop with a ring of S column chunks instead of S blocks
-// The prefetch distance is counted in 16-column chunks (FP32; 32 columns
-// for BF16): a row of narrow blocks (rank 16 or 27, leaves of 32) keeps
+// The prefetch distance is counted in 16-column chunks: a row of narrow blocks (rank 16 or 27, leaves of 32) keeps
 // S / 2 or more blocks in flight where a block ring would keep D, for the
 // registers of S chunks (a quarter of a full-width block each).  The chunks
 // of the row's blocks are consumed in order; slot s holds chunk i of the row
 // when i = s (mod S), and is refilled with chunk i + S as soon as its
-// products are issued.  A block's sum (times its BF16 scale) is added to the
+// products are issued.  A block's sum is added to the
 // FP64 totals after its last chunk, so the arithmetic and its order are those
 // of mm_row16 (bitwise the same results).
-template <int KIND>
 struct Chunk16 {
-    typename std::conditional<KIND == ELEM_F32, f32x4, u32x4>::type a[2];   // per row tile
-    f32x4 b[KIND == ELEM_F32 ? 1 : 2];
+    f32x4 a[2];   // per row tile
+    f32x4 b;
 };
-template <int KIND>
 __device__ inline void load_one_chunk16(const BlkDesc &bd, const void *blk, const float *xbase, int R,
-                                        const int (&ic)[2], int n, int kq, int c, bool live, Chunk16<KIND> &o) {
-    BlockA16<KIND> a;
+                                        const int (&ic)[2], int n, int kq, int c, bool live, Chunk16 &o) {
+    BlockA16 a;
     TileB16 b;
-    load_chunk16<KIND>(bd, blk, xbase, R, ic, n, kq, c, live, a, b);
+    load_chunk16(bd, blk, xbase, R, ic, n, kq, c, live, a, b);
 #pragma unroll
     for (int h = 0; h < 2; ++h) o.a[h] = a.v[h][c];
-    if constexpr (KIND == ELEM_F32) {
-        o.b[0] = b.v[c];
-    } else {
-        o.b[0] = b.v[2 * c];
-        o.b[1] = b.v[2 * c + 1];
-    }
+    o.b = b.v[c];
 }
-template <int KIND>
-__device__ inline void one_chunk_products16(const Chunk16<KIND> &o, int c, int Cp, int nh, int kq, f32x4 (&acc)[2]) {
-    BlockA16<KIND> a;
+__device__ inline void one_chunk_products16(const Chunk16 &o, int c, int nh, f32x4 (&acc)[2]) {
+    BlockA16 a;
     TileB16 b;
 #pragma unroll
     for (int h = 0; h < 2; ++h) a.v[h][c] = o.a[h];
-    if constexpr (KIND == ELEM_F32) {
-        b.v[c] = o.b[0];
-    } else {
-        b.v[2 * c] = o.b[0];
-        b.v[2 * c + 1] = o.b[1];
-    }
-    chunk_products16<KIND>(a, b, c, Cp, nh, kq, acc);
+    b.v[c] = o.b;
+    chunk_products16(a, b, c, nh, acc);
 }
 
-template <int KIND, bool LEAF, bool BATCH, int S>
+template <bool LEAF, bool BATCH, int S>
 __device__ inline void mm_row16_cring(const MmArgs &g, int64_t row, int mt, int lane) {
     const RowDesc rd = g.rows[row];
     const int R = rd.R;
@@ -1003,7 +886,7 @@ __device__ inline void mm_row16_cring(const MmArgs &g, int64_t row, int mt, int 
     const float *xbase = (rd.sel & ROW_IN_X) ? g.in_pts : g.in_tree;
     auto block_ptr = [&](const BlkDesc &bd) -> const void * {
         if constexpr (BATCH) return reinterpret_cast<const void *>(bd.a);
-        else return static_cast<const char *>(g.data) + bd.a * (KIND == ELEM_F32 ? 4 : 2);
+        else return static_cast<const char *>(g.data) + bd.a * 4;
     };
 
     double tot[2][4];
@@ -1014,24 +897,24 @@ __device__ inline void mm_row16_cring(const MmArgs &g, int64_t row, int mt, int 
 
     const int nb = rd.b1 - rd.b0;
     if (nb > 0) {
-        LaneDescs<KIND> ld;
+        LaneDescs<ELEM_F32> ld;
         ld.load(g, rd, nb, lane);
         // consumption cursor: chunk c of block k (descriptor bk); refill
         // cursor: chunk c2 of block k2 (descriptor bk2), S chunks ahead
         int k = 0, c = 0, k2 = 0, c2 = 0;
         BlkDesc bk = ld.get(g, rd, 0), bk2 = bk;
-        int np = used_chunks16<KIND>(bk.C), np2 = np;
+        int np = used_chunks16(bk.C), np2 = np;
         int total = 0;   // chunks in the row
-        for (int j = 0; j < nb; ++j) total += used_chunks16<KIND>(ld.get(g, rd, j).C);
-        Chunk16<KIND> ring[S];
+        for (int j = 0; j < nb; ++j) total += used_chunks16(ld.get(g, rd, j).C);
+        Chunk16 ring[S];
         auto refill = [&](int s) {
             const bool live = k2 < nb;   // wave-uniform
-            load_one_chunk16<KIND>(bk2, block_ptr(bk2), xbase, R, ic, n, kq, live ? c2 : 0, live, ring[s]);
+            load_one_chunk16(bk2, block_ptr(bk2), xbase, R, ic, n, kq, live ? c2 : 0, live, ring[s]);
             if (live && ++c2 == np2) {
                 c2 = 0;
                 if (++k2 < nb) {
                     bk2 = ld.get(g, rd, k2);
-                    np2 = used_chunks16<KIND>(bk2.C);
+                    np2 = used_chunks16(bk2.C);
                 }
             }
         };
@@ -1041,7 +924,7 @@ __device__ inline void mm_row16_cring(const MmArgs &g, int64_t row, int mt, int 
 #pragma unroll
         for (int h = 0; h < 2; ++h) acc[h] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         auto step = [&](int s) {
-            one_chunk_products16<KIND>(ring[s], c, round16(bk.C), nh, kq, acc);
+            one_chunk_products16(ring[s], c, nh, acc);
             refill(s);
             if (++c == np) {   // the block's last chunk: its sum goes to the totals
                 const double sc = ld.scale(g, k, bk);
@@ -1056,7 +939,7 @@ __device__ inline void mm_row16_cring(const MmArgs &g, int64_t row, int mt, int 
                 c = 0;
                 if (++k < nb) {
                     bk = ld.get(g, rd, k);
-                    np = used_chunks16<KIND>(bk.C);
+                    np = used_chunks16(bk.C);
                 }
             }
         };
@@ -1301,9 +1184,9 @@ __device__ inline void mm_body(const MmArgs &g) {
     const int64_t nwg = g.nitems >> 2;
     auto one = [&](int32_t it) {
         if constexpr (NT == 16) {
-            if constexpr (PIPE >= 6) mm_row16_cring<KIND, LEAF, BATCH, PIPE == 6 ? 6 : 8>(g, it >> 1, it & 1, lane);
-            else if constexpr (PIPE >= 2) mm_row16_ring<KIND, LEAF, BATCH, PIPE>(g, it >> 1, it & 1, lane);
-            else mm_row16<KIND, LEAF, BATCH, PIPE == 1>(g, it >> 1, it & 1, lane);
+            if constexpr (PIPE >= 6) mm_row16_cring<LEAF, BATCH, PIPE == 6 ? 6 : 8>(g, it >> 1, it & 1, lane);
+            else if constexpr (PIPE >= 2) mm_row16_ring<LEAF, BATCH, PIPE>(g, it >> 1, it & 1, lane);
+            else mm_row16<LEAF, BATCH, PIPE == 1>(g, it >> 1, it & 1, lane);
         } else {
             if constexpr (PIPE >= 2) mm_row_ring<KIND, LEAF, BATCH, PIPE>(g, it >> 1, it & 1, lane);
             else mm_row<KIND, LEAF, BATCH, PIPE == 1>(g, it >> 1, it & 1, lane);
@@ -1350,9 +1233,11 @@ H2_MM_PHASE_KERNEL(mm_leafexpand_kernel, true)
 
 #include "h2_mm16.h"
 
-// Copies right-hand sides j0 .. j0+NT-1 of the caller's column-major FP64 X
+// Copies right-hand sides j0 .. j0+TW-1 of the caller's column-major FP64 X
 // into point tiles: leaf j at j * slot, [rhs][row] with a leading dimension of
-// its size rounded up to 16, zero-padded (rows and missing right-hand sides).
+// its size rounded up to 16 (TW = 16: tile16), zero-padded (rows and missing
+// right-hand sides).
+template <int TW>
 __global__ __launch_bounds__(256) void pack_kernel(const double *__restrict__ X, int64_t ldx, int j0, int nrhs,
                                                    const int64_t *__restrict__ leaf_begin,
                                                    const int64_t *__restrict__ leaf_end, int64_t slot,
@@ -1366,23 +1251,24 @@ __global__ __launch_bounds__(256) void pack_kernel(const double *__restrict__ X,
     // a thread's loads are issued before its stores)
     const int c = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (c >= mp) return;
-    float v[NT / 4];
+    float v[TW / 4];
 #pragma unroll
-    for (int k = 0; k < NT / 4; ++k) {
+    for (int k = 0; k < TW / 4; ++k) {
         const int j = w + 4 * k;
         v[k] = c < m && j0 + j < nrhs ? float(X[(b + c) + int64_t(j0 + j) * ldx]) : 0.0f;
     }
 #pragma unroll
-    for (int k = 0; k < NT / 4; ++k) t[int64_t(w + 4 * k) * mp + c] = v[k];
+    for (int k = 0; k < TW / 4; ++k) t[TW == 16 ? tile16(c, w + 4 * k) : (w + 4 * k) * mp + c] = v[k];
 }
 
 }  // namespace
 
 hipError_t launch_pack(const double *X, int64_t ldx, int j0, int nrhs, const int64_t *leaf_begin,
-                       const int64_t *leaf_end, int64_t nleaves, int64_t slot, float *tiles, hipStream_t st) {
+                       const int64_t *leaf_end, int64_t nleaves, int64_t slot, float *tiles, int tile_width,
+                       hipStream_t st) {
     if (nleaves <= 0) return hipSuccess;
-    hipLaunchKernelGGL(pack_kernel, dim3(unsigned(nleaves)), dim3(256), 0, st, X, ldx, j0, nrhs, leaf_begin,
-                       leaf_end, slot, tiles);
+    hipLaunchKernelGGL(tile_width == 16 ? pack_kernel<16> : pack_kernel<NT>, dim3(unsigned(nleaves)), dim3(256), 0, st,
+                       X, ldx, j0, nrhs, leaf_begin, leaf_end, slot, tiles);
     return hipGetLastError();
 }
 
@@ -1452,7 +1338,7 @@ hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg
     if ((pair || phase == PHASE_STREAM) && (L.npitems <= 0 || L.npitems % (2 * MM_XCDS) != 0)) return hipErrorInvalidValue;
     MmArgs g{L.rows, pair ? L.pitems : L.items, pair ? L.npitems : L.nitems, L.blks, L.data, L.scales, L.in_tree,
              L.in_pts, L.init, L.out_tree, L.out_pts, L.Y, L.ldy, nullptr, nullptr, L.ncols};
-    const int nt = cfg.nt == 32 || L.ncols > 16 ? 32 : 16;
+    const int nt = mm_tile_width(cfg, L.ncols);
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
     if (phase == PHASE_STREAM && nt == 16) launch_narrow<false>(g, kind, L.pitems, L.npitems, st);
     else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<false, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
@@ -1469,7 +1355,7 @@ hipError_t launch_mm_batch(const MmBatchLaunch &L, int kind, int phase, const Mm
     MmArgs g{L.rows, pair ? L.pitems : L.items, pair ? L.npitems : L.nitems, L.blks, nullptr, L.scales, L.pool,
              L.pool, L.pool, L.pool, L.pool, nullptr, 0, L.Ytab, L.ldytab, L.ncols};
     if (L.ncols < 1 || L.ncols > MM_TILE) return hipErrorInvalidValue;
-    const int nt = cfg.nt == 32 || L.ncols > 16 ? 32 : 16;
+    const int nt = mm_tile_width(cfg, L.ncols);
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
     if (phase == PHASE_STREAM && nt == 16) launch_narrow<true>(g, kind, L.pitems, L.npitems, st);
     else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<true, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
@@ -1489,7 +1375,7 @@ hipError_t launch_mm_batch(const MmBatchLaunch &L, int kind, int phase, const Mm
 __global__ __launch_bounds__(256) void batch_pack_kernel(const PackEntry *__restrict__ entries, int64_t count,
                                                          double const *const *__restrict__ Xtab,
                                                          const int64_t *__restrict__ ldxtab, int nrhs,
-                                                         float *__restrict__ pool) {
+                                                         int tile_width, float *__restrict__ pool) {
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), c = threadIdx.x & 63;
     const int nc = nrhs < NT ? nrhs : NT;
     for (int64_t k = int64_t(blockIdx.x) * 4 + wv; k < count; k += int64_t(gridDim.x) * 4) {
@@ -1509,18 +1395,19 @@ __global__ __launch_bounds__(256) void batch_pack_kernel(const PackEntry *__rest
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (j0 + u < nc) t[int64_t(j0 + u) * mp + c] = c < e.m ? v[u] : 0.0f;
+                if (j0 + u < nc) t[tile_width == 16 ? tile16(c, j0 + u) : (j0 + u) * mp + c] = c < e.m ? v[u] : 0.0f;
         }
     }
 }
 
 hipError_t launch_batch_pack(const PackEntry *entries, int64_t count, double const *const *Xtab,
-                             const int64_t *ldxtab, int nrhs, float *pool, int64_t grid, hipStream_t st) {
+                             const int64_t *ldxtab, int nrhs, int tile_width, float *pool, int64_t grid,
+                             hipStream_t st) {
     if (count <= 0) return hipSuccess;
     const int64_t wgs = (count + 3) / 4;
     const int64_t g = grid > 0 && grid < wgs ? grid : wgs;
     hipLaunchKernelGGL(batch_pack_kernel, dim3(unsigned(g)), dim3(256), 0, st, entries, count, Xtab, ldxtab, nrhs,
-                       pool);
+                       tile_width, pool);
     return hipGetLastError();
 }
 

@@ -18,14 +18,14 @@
 // multiplication, and what consuming a chunk needs to know of its block (its
 // last chunk, its scale) is kept with the ring slot.  A block's products and
 // their order are those of the other loops.
-// 8 right-hand sides, streaming launch, before (best of the 32-row loops) and
-// now: 2-D 400,000 points FP32 1.78 -> 1.63 ms (4.8 TB/s of block bytes), 3-D
-// 50,021 points of rank 27 BF16 402 -> 317 us; whole products of 4,096 points
-// 63 -> 50 us, of a batch of 24 at FP32 975 -> 840 us.  Insensitive to S (2 to
-// 10) and to two to four wavefronts per SIMD; the L1 caches' address
-// processing is busy 82 % of the time (256-byte runs that start anywhere, for
-// the blocks; 64-byte ones for the tiles: reading a fixed 1 KiB instead of
-// them gains 5 to 14 %).
+// 8 right-hand sides, whole products, the 32-row loops with their best launch
+// shape against this one (tiles as then): 2-D 400,000 points FP32 2.13 -> 1.99
+// ms, 4,096 points 63 -> 50 us, 3-D 50,021 points of rank 27 BF16 443 -> 393
+// us, batch of 24 FP32 1000 -> 835 us.  Insensitive to S (2 to 10) and to two
+// to four wavefronts per SIMD; bound by the L1 caches' address processing
+// (busy 82 % of the time before the tiles' rows were put together): 256-byte
+// runs of block items that start anywhere, five per KiB of a chunk where rows
+// are ragged.
 
 constexpr int kNarrowWaves = 4;
 
@@ -86,7 +86,6 @@ __device__ __forceinline__ void narrow_blocks(const MmArgs &g, const RowDesc &rd
         const uint32_t live = k < cnt ? ~0u : 0u;   // past the end: one item of the last block, unused
         const int groups = (C + W - 1) / W - (CH / W) * c;   // item columns from this chunk on
         const uint32_t ko = uint32_t(kq < groups ? kq : groups - 1) * R16;
-        const int Cp = round16(C);
         typedef const __attribute__((address_space(1))) char *gptr;
         typedef typename std::conditional<KIND == ELEM_F32, f32x4, u32x4>::type item;
 #pragma unroll
@@ -95,20 +94,20 @@ __device__ __forceinline__ void narrow_blocks(const MmArgs &g, const RowDesc &rd
                 reinterpret_cast<const __attribute__((address_space(1))) item *>((gptr)ap + ((ko + ro[h]) & live)));
         last[s] = c + 1 == np;
         if constexpr (KIND == ELEM_F32) {
-            const uint32_t xo = uint32_t(n * Cp) * 4 + uint32_t(kq) * 16;
+            const uint32_t xo = uint32_t(kq * 16 + n) * 16;
             ring[s].b[0] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo);
         } else {
-            rem[s] = Cp - CH * c;
+            rem[s] = round16(C) - CH * c;
             const int col = 8 * kq < rem[s] ? 8 * kq : rem[s] - 8;
-            const uint32_t xo = uint32_t(n * Cp + col) * 4;
+            const uint32_t xo = uint32_t(col * 4 + n) * 16;
             ring[s].b[0] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo);
-            ring[s].b[1] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo + 16);
+            ring[s].b[1] = *reinterpret_cast<const __attribute__((address_space(1))) f32x4 *>((gptr)xp + xo + 256);
             sc[s] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mysc), k & 63));
         }
         if (live) {
             if (++c < np) {
                 ap += (CH / W) * R16;
-                xp += CH * 4;
+                xp += CH * 64;
             } else if (++k < cnt) {
                 if ((k & 63) == 0) load_descs(k);
                 c = 0;
@@ -222,6 +221,6 @@ __global__ __launch_bounds__(64 * kNarrowWaves) void mm_stream_narrow_kernel(MmA
     f32x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = i0 + e < R ? float(v[e]) : 0.0f;
-    float *out = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + int64_t(n) * Rp + i0;
+    float *out = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + tile16(i0, n);
     *reinterpret_cast<f32x4 *>(out) = o;
 }

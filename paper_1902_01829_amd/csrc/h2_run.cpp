@@ -175,7 +175,8 @@ void run_tile_pass(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64
     const int64_t nleaves = int64_t(1) << A.st.q;
     {
         check_hip(h2::launch_pack(X, ldx, j0, nrhs, A.d_leaf_begin, A.d_leaf_end, nleaves, A.tile_slot,
-                                  static_cast<float *>(A.t_x), st),
+                                  static_cast<float *>(A.t_x),
+                                  h2::mm_tile_width(cfg, std::min(h2::MM_TILE, nrhs - j0)), st),
                   "pack launch");
         run_lists(A, A.mm_lists, st, [&](const WorkList &w) {
             h2::MmLaunch L;
