@@ -74,26 +74,22 @@ void store_config(const std::string &sig, const h2::MmConfig &cfg) {
     }
 }
 
-// Launch shapes the tuners try.  Passes of more than 16 right-hand sides: the
-// block loop's prefetch depth (0 plain, 1 the next block, 2 and 3 rings of
-// block slots in registers, 4 and 5 rings with a row's halves sharing the
-// input tile) with several grids.  Passes of at most 16 run the streaming
-// launch one way, so that only the sweeps' depth is left to choose: 16-wide
-// tiles, plain, a ring of 2 blocks or of 6 column chunks, one workgroup per 4
-// items (the other depths, persistent grids and 32-wide tiles were never the
-// fastest by more than 1 % with this streaming launch; the first product of a
-// batch of 24 took 183 ms with all of them, 8.6 ms with these, that of a 3-D
-// matrix of 50,021 points 59 and 2.9 ms).
-std::vector<h2::MmConfig> tile_candidates(int ncols, std::initializer_list<int64_t> grids) {
+// Launch shapes the tuners try: the block loops' prefetch depth, one workgroup
+// per 4 items (tile sharing: per 2).  Passes of at most 16 right-hand sides
+// run the streaming launch one way, so that only the sweeps' depth is left:
+// 16-wide tiles, plain, a ring of 2 blocks or of 6 column chunks.  Wider ones:
+// plain, and rings of 1 and 2 blocks with a row's halves sharing the input
+// tile.  (The other depths, persistent grids and 32-wide tiles for narrow
+// passes were never the fastest by more than 2 %; the first product of a batch
+// of 24 with 8 right-hand sides took 183 ms with all of them, 8.6 ms with
+// these, that of 524,288 points with 32 right-hand sides 137 and 22 ms.)
+std::vector<h2::MmConfig> tile_candidates(int ncols) {
     if (ncols <= 16) return {{0, 0, 16}, {2, 0, 16}, {6, 0, 16}};
-    std::vector<h2::MmConfig> c;
-    for (int pipe = 0; pipe < h2::MM_FIRST_CRING; ++pipe)
-        for (int64_t grid : grids) c.push_back({pipe, grid, 32});
-    return c;
+    return {{0, 0, 32}, {4, 0, 32}, {5, 0, 32}};
 }
 
 // Times every candidate configuration on the batch (tables set) and keeps the
-// fastest (persistent grids: 1, 2 and 4 workgroups per compute unit).
+// fastest.
 void batch_autotune(h2_batch_ &B) {
     h2::MmConfig best{1, 0, 0};
     if (cached_config(B.signature, best)) {
@@ -105,8 +101,7 @@ void batch_autotune(h2_batch_ &B) {
     check_hip(hipEventCreate(&t0), "hipEventCreate");
     check_hip(hipEventCreate(&t1), "hipEventCreate");
     double best_ms = 1e30;
-    const int64_t cu = (B.cu_count + h2::MM_XCDS - 1) / h2::MM_XCDS * h2::MM_XCDS;
-    for (const h2::MmConfig &c : tile_candidates(B.nrhs, {0, cu, 2 * cu, 4 * cu})) {
+    for (const h2::MmConfig &c : tile_candidates(B.nrhs)) {
         batch_enqueue(B, c, B.own);   // warm-up
         float ms_best = 1e30f;
         for (int rep = 0; rep < 2; ++rep) {
@@ -305,11 +300,7 @@ void tune_tiles(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t 
         check_hip(hipEventCreate(&t0), "hipEventCreate");
         check_hip(hipEventCreate(&t1), "hipEventCreate");
         float bms = 1e30f;
-        int dev = 0, cus = 256;
-        check_hip(hipGetDevice(&dev), "hipGetDevice");
-        check_hip(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device attribute");
-        const int64_t cu = (cus + h2::MM_XCDS - 1) / h2::MM_XCDS * h2::MM_XCDS;
-        for (const h2::MmConfig &c : tile_candidates(ncols, {0, cu, 2 * cu})) {
+        for (const h2::MmConfig &c : tile_candidates(ncols)) {
             run_tile_pass(A, X, ldx, Y, ldy, nrhs, j0, c, st);   // warm-up
             check_hip(hipEventRecord(t0, st), "hipEventRecord");
             run_tile_pass(A, X, ldx, Y, ldy, nrhs, j0, c, st);

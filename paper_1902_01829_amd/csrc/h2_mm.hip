@@ -4,8 +4,10 @@
 // k x r tile and every block product a dense contraction (R x C block) x
 // (C x r tile).  The phases, work lists and block layout are those of the
 // single-vector product; only the arithmetic changes:
-//   - tiles hold 32 right-hand sides (one MFMA N dimension), FP32, stored
-//     [rhs][row] with a leading dimension rounded up to 16 rows (zero-padded);
+//   - tiles hold 32 right-hand sides (one MFMA N dimension), FP32, rows rounded
+//     up to 16 (zero-padded), four rows of one right-hand side together
+//     (tile_at), so that the 16-byte values a wavefront reads or writes at a
+//     time are runs of 256 bytes or more and not 16 or 32 pieces;
 //   - FP32 blocks: v_mfma_f32_32x32x2_f32 on FP32 operands.  (Splitting both
 //     operands into two BF16 pieces each for the faster BF16 MFMA drops bits
 //     of the products: measured 2.5e-6 against 4.7e-7 on 2^20 points.)
@@ -38,6 +40,14 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int NT = MM_TILE;   // right-hand sides per tile
 
 __device__ inline int round16(int v) { return (v + 15) & ~15; }
+
+// Place of row r, right-hand side n in a tile of TW right-hand sides.  (Rows
+// of a right-hand side side by side instead: 32 right-hand sides, 3-D 50,021
+// points BF16 652 -> 526 us, batch of 24 FP32 1260 -> 1064 us, 2-D 524,288
+// points 2.54 -> 2.49 ms; 8 right-hand sides, batch of 24 847 -> 783 us, 2-D
+// 400,000 points 1.99 -> 1.86 ms.)
+template <int TW>
+__device__ inline int tile_at(int r, int n) { return ((r >> 2) * TW + n) * 4 + (r & 3); }
 
 // Non-temporal 16-byte load of block data through a global-address-space
 // pointer: batches hold block addresses as integers, and a generic pointer
@@ -95,14 +105,14 @@ __device__ inline void load_a(const BlkDesc &bd, const void *blk, int R, int ic,
 
 template <int KIND>
 __device__ inline void load_b(const BlkDesc &bd, const float *xbase, int li, int lg, TileB &o) {
-    const int Cp = round16(bd.C), NP = Cp >> 3;
-    const float *xb = xbase + bd.in + li * Cp;
+    const int NP = round16(bd.C) >> 3;
+    const float *xb = xbase + bd.in;
 #pragma unroll
     for (int p = 0; p < 8; ++p) {
         if (p >= NP) break;
         // FP32 blocks: columns 8p + 4g .. +3; BF16 blocks: step p/2, half p%2
         const int col = KIND == ELEM_F32 ? 8 * p + 4 * lg : 16 * (p >> 1) + 8 * lg + 4 * (p & 1);
-        o.v[p] = *reinterpret_cast<const f32x4 *>(xb + col);
+        o.v[p] = *reinterpret_cast<const f32x4 *>(xb + tile_at<32>(col, li));
     }
 }
 
@@ -307,11 +317,11 @@ template <int KIND>
 __device__ inline void load_chunk32(const BlkDesc &bd, const void *blk, const float *xbase, int R, int ic, int li,
                                     int lg, int p, bool live, BlockA<KIND> &a, TileB &b) {
     const int C = bd.C, Cp = round16(C);
-    const float *xb = xbase + bd.in + li * Cp;
+    const float *xb = xbase + bd.in;
     if constexpr (KIND == ELEM_F32) {
         const int CW = (C + 3) >> 2, cg = 2 * p + lg, cgc = cg < CW ? cg : CW - 1;
         const int col = 8 * p + 4 * lg, colc = col < Cp ? col : Cp - 4;
-        const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + colc);
+        const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + tile_at<32>(colc, li));
         const f32x4 *ap = live ? reinterpret_cast<const f32x4 *>(static_cast<const float *>(blk) +
                                                                  (int64_t(cgc) * R + ic) * 4)
                                : reinterpret_cast<const f32x4 *>(xbase + bd.in);
@@ -320,13 +330,13 @@ __device__ inline void load_chunk32(const BlkDesc &bd, const void *blk, const fl
     } else {
         const int CW = (C + 7) >> 3, cg = 2 * p + lg, cgc = cg < CW ? cg : CW - 1;
         const int col = 16 * p + 8 * lg, colc = col < Cp ? col : Cp - 8;
-        const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + colc);
+        const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + tile_at<32>(colc, li));
         const u32x4 *ap = live ? reinterpret_cast<const u32x4 *>(static_cast<const uint16_t *>(blk) +
                                                                  (int64_t(cgc) * R + ic) * 8)
                                : reinterpret_cast<const u32x4 *>(xbase + bd.in);
         a.v[p] = load_block_item(ap);
         b.v[2 * p] = bp[0];
-        b.v[2 * p + 1] = bp[1];
+        b.v[2 * p + 1] = bp[32];
     }
 }
 
@@ -366,7 +376,7 @@ __device__ inline void mm_store32(const MmArgs &g, const RowDesc &rd, int mt, in
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int i0 = 32 * mt + 8 * q + 4 * lg, i0c = i0 < Rp ? i0 : Rp - 4;
-            t[q] = *reinterpret_cast<const f32x4 *>(g.init + rd.init + int64_t(lic) * Rp + i0c);
+            t[q] = *reinterpret_cast<const f32x4 *>(g.init + rd.init + tile_at<32>(i0c, lic));
         }
     }
 #pragma unroll
@@ -390,7 +400,7 @@ __device__ inline void mm_store32(const MmArgs &g, const RowDesc &rd, int mt, in
             if (rd.init >= 0) {
                 v[0] += t[q].x; v[1] += t[q].y; v[2] += t[q].z; v[3] += t[q].w;
             }
-            float *o = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + int64_t(li) * Rp + i0;
+            float *o = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + tile_at<32>(i0, li);
             *reinterpret_cast<f32x4 *>(o) = f32x4{float(v[0]), float(v[1]), float(v[2]), float(v[3])};
         }
     }
@@ -420,7 +430,7 @@ __device__ inline void mm_store32_leaf_lds(const MmArgs &g, const RowDesc &rd, i
 #pragma unroll
         for (int c = 0; c < 16; ++c) {
             const int j = 2 * c + lg, jc = j < g.ncols ? j : g.ncols - 1;
-            yn[c] = g.init[rd.init + int64_t(jc) * Rp + ic];
+            yn[c] = g.init[rd.init + tile_at<32>(ic, jc)];
         }
     }
 #pragma unroll
@@ -519,20 +529,13 @@ __device__ inline void mm_row_ring(const MmArgs &g, int64_t row, int mt, int lan
 
 // ---- 16 right-hand sides (passes of at most 16 columns, batches of <= 16):
 // the sweeps (FP32 bases); the streaming launch has a loop of its own below.
-// Tiles of these passes hold 16 right-hand sides, four rows of one right-hand
-// side together: row r of right-hand side n at ((r / 4) * 16 + n) * 4 + r % 4,
-// so that the 16-byte values of a wavefront (lane l: right-hand side l % 16,
-// rows 4 (l / 16) .. + 3 of 16) are one run of 1 KiB and not 16 of 64 bytes
-// (8 right-hand sides, FP32: batch of 24 847 -> 783 us, 2-D 400,000 points
-// 1.99 -> 1.86 ms; 3-D 50,021 points BF16 384 -> 363 us).
+// Tiles of these passes hold 16 right-hand sides.
 // A wavefront owns a 32-row half of an output segment, as two 16-row MFMA
 // tiles h = 0, 1: lane l owns block row 32*mt + 16*h + (l % 16) and
 // right-hand side l % 16, and lane group q = l / 16 supplies K values:
 // v_mfma_f32_16x16x4_f32; per 16 block columns, lane group q loads the 4
 // columns 16c + 4q .. 16c + 4q + 3 (one 16-byte item) and step t uses column
 // 16c + 4q + t.
-__device__ inline int tile16(int r, int n) { return ((r >> 2) * 16 + n) * 4 + (r & 3); }
-
 struct BlockA16 {
     f32x4 v[2][4];   // [row tile][16-column chunk]
 };
@@ -562,7 +565,7 @@ __device__ inline void load_b16(const BlkDesc &bd, const float *xbase, int n, in
 #pragma unroll
     for (int c = 0; c < 4; ++c) {
         if (c >= NC) break;
-        o.v[c] = *reinterpret_cast<const f32x4 *>(xb + tile16(16 * c + 4 * kq, n));
+        o.v[c] = *reinterpret_cast<const f32x4 *>(xb + tile_at<16>(16 * c + 4 * kq, n));
     }
 }
 
@@ -679,7 +682,7 @@ __device__ inline void load_chunk16(const BlkDesc &bd, const void *blk, const fl
     const float *xb = xbase + bd.in;
     const int CW = (C + 3) >> 2, cg = 4 * c + kq, cgc = cg < CW ? cg : CW - 1;
     const int col = 16 * c + 4 * kq, colc = col < Cp ? col : Cp - 4;
-    const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + tile16(colc, n));
+    const f32x4 *bp = reinterpret_cast<const f32x4 *>(xb + tile_at<16>(colc, n));
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
         const f32x4 *ap = live ? reinterpret_cast<const f32x4 *>(static_cast<const float *>(blk) +
@@ -713,7 +716,7 @@ __device__ inline void mm_store16(const MmArgs &g, const RowDesc &rd, int mt, in
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
                 const int j = 2 * c + jp, jc = j < g.ncols ? j : g.ncols - 1;
-                yn[c] = g.init[rd.init + tile16(ic, jc)];
+                yn[c] = g.init[rd.init + tile_at<16>(ic, jc)];
             }
         }
 #pragma unroll
@@ -741,7 +744,7 @@ __device__ inline void mm_store16(const MmArgs &g, const RowDesc &rd, int mt, in
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int i0 = 32 * mt + 16 * h + 4 * kq, i0c = i0 < Rp ? i0 : Rp - 4;
-                t[h] = *reinterpret_cast<const f32x4 *>(g.init + rd.init + tile16(i0c, n));
+                t[h] = *reinterpret_cast<const f32x4 *>(g.init + rd.init + tile_at<16>(i0c, n));
             }
         }
 #pragma unroll
@@ -755,7 +758,7 @@ __device__ inline void mm_store16(const MmArgs &g, const RowDesc &rd, int mt, in
             if (rd.init >= 0) {
                 v[0] += t[h].x; v[1] += t[h].y; v[2] += t[h].z; v[3] += t[h].w;
             }
-            float *o = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + tile16(i0, n);
+            float *o = ((rd.sel & ROW_OUT_P) ? g.out_pts : g.out_tree) + rd.out + tile_at<16>(i0, n);
             *reinterpret_cast<f32x4 *>(o) = f32x4{float(v[0]), float(v[1]), float(v[2]), float(v[3])};
         }
     }
@@ -977,7 +980,7 @@ __device__ inline void lds_barrier() {
 }
 
 // This wavefront's half of the tile of block bd: load t of lane l takes
-// right-hand side 16*mt + 4t + l/16 and columns 4*(l % 16) .. + 3, the
+// right-hand side 16*mt + l % 16 and columns 16t + 4*(l / 16) .. + 3, the
 // column group clamped to the tile's last one for narrow tiles (duplicates
 // of valid items, written to the same LDS place).  With live == false the
 // loads re-read the first items.  (Shifts and masks only: this index math
@@ -987,8 +990,8 @@ struct TileHalf {
     f32x4 v[4];
 };
 __device__ inline void half_index(int Cp, int mt, int lane, int t, int &r, int &c) {
-    const int cg = lane & 15, last = (Cp >> 2) - 1;
-    r = 16 * mt + 4 * t + (lane >> 4);
+    const int cg = 4 * t + (lane >> 4), last = (Cp >> 2) - 1;
+    r = 16 * mt + (lane & 15);
     c = 4 * (cg < last ? cg : last);
 }
 __device__ inline void load_half(const BlkDesc &bd, const float *xbase, int mt, int lane, bool live, TileHalf &h) {
@@ -997,7 +1000,7 @@ __device__ inline void load_half(const BlkDesc &bd, const float *xbase, int mt, 
     for (int t = 0; t < 4; ++t) {
         int r, c;
         half_index(Cp, mt, lane, t, r, c);
-        const float *p = xbase + bd.in + (live ? r * Cp + c : 4 * t);
+        const float *p = xbase + bd.in + (live ? tile_at<32>(c, r) : 4 * t);
         h.v[t] = *reinterpret_cast<const f32x4 *>(p);
     }
 }
@@ -1231,12 +1234,11 @@ H2_MM_PHASE_KERNEL(mm_downsweep_kernel, false)
 H2_MM_PHASE_KERNEL(mm_leafexpand_kernel, true)
 #undef H2_MM_PHASE_KERNEL
 
-#include "h2_mm16.h"
+#include "h2_mmstream.h"
 
 // Copies right-hand sides j0 .. j0+TW-1 of the caller's column-major FP64 X
-// into point tiles: leaf j at j * slot, [rhs][row] with a leading dimension of
-// its size rounded up to 16 (TW = 16: tile16), zero-padded (rows and missing
-// right-hand sides).
+// into point tiles: leaf j at j * slot (tile_at), zero-padded (rows and
+// missing right-hand sides).
 template <int TW>
 __global__ __launch_bounds__(256) void pack_kernel(const double *__restrict__ X, int64_t ldx, int j0, int nrhs,
                                                    const int64_t *__restrict__ leaf_begin,
@@ -1258,7 +1260,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const double *__restrict__ X,
         v[k] = c < m && j0 + j < nrhs ? float(X[(b + c) + int64_t(j0 + j) * ldx]) : 0.0f;
     }
 #pragma unroll
-    for (int k = 0; k < TW / 4; ++k) t[TW == 16 ? tile16(c, w + 4 * k) : (w + 4 * k) * mp + c] = v[k];
+    for (int k = 0; k < TW / 4; ++k) t[tile_at<TW>(c, w + 4 * k)] = v[k];
 }
 
 }  // namespace
@@ -1285,7 +1287,7 @@ static void launch_phase_nt(const MmArgs &g, int kind, int phase, unsigned grid,
     case PHASE_LEAF:
         hipLaunchKernelGGL((mm_leafexpand_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
         break;
-    default:   // (16-wide: launch_narrow)
+    default:   // (16-wide: launch_stream_tiles)
         if constexpr (NT == 32) {
             if (kind == ELEM_F32)
                 hipLaunchKernelGGL((mm_stream_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
@@ -1319,14 +1321,26 @@ static void launch_phase(const MmArgs &g, int kind, int phase, int nt, int depth
     }
 }
 
-// The streaming launch of a pass of at most 16 right-hand sides.
-template <bool BATCH>
-static void launch_narrow(const MmArgs &g, int kind, const int32_t *pitems, int64_t npitems, hipStream_t st) {
-    const dim3 grid(unsigned(npitems / 2)), block(64 * kNarrowWaves);
+// Whether the streaming launch runs mm_stream_tiles_kernel: always for 16-wide
+// tiles.  For 32-wide ones, where a wavefront of it holds 200 registers, in
+// short lists, whose long rows it spreads over four wavefronts, and in FP32
+// batches; else the block loops above with the tuned depth (32 right-hand
+// sides, loops against it: FP32 2-D 30,000 points (3,032 items) 234 / 213 us,
+// 60,000 (6,104) 394 / 389 us, 524,288 (49,112) 2.49 / 2.56 ms, 3-D 200,000
+// points 2.81 / 3.00 ms, batch of 24 1.06 / 1.01 ms; BF16 2-D 60,000 points
+// 272 / 274 us, 3-D 9,000 points (1,100) 280 / 203 us, 50,021 (6,077) 526 / 598
+// us).
+static bool stream_by_tiles(int tile_width, int kind, bool batch, int64_t npitems) {
+    return tile_width == 16 || (kind == ELEM_F32 ? batch || npitems <= 8192 : npitems <= 4096);
+}
+
+template <bool BATCH, int TW>
+static void launch_stream_tiles(const MmArgs &g, int kind, const int32_t *pitems, int64_t npitems, hipStream_t st) {
+    const dim3 grid(unsigned(npitems / 2)), block(64 * kStreamWaves);
     if (kind == ELEM_F32)
-        hipLaunchKernelGGL((mm_stream_narrow_kernel<ELEM_F32, BATCH>), grid, block, 0, st, g, g.rows, g.blks, pitems, g.scales);
+        hipLaunchKernelGGL((mm_stream_tiles_kernel<ELEM_F32, BATCH, TW>), grid, block, 0, st, g, g.rows, g.blks, pitems, g.scales);
     else
-        hipLaunchKernelGGL((mm_stream_narrow_kernel<ELEM_BF16, BATCH>), grid, block, 0, st, g, g.rows, g.blks, pitems, g.scales);
+        hipLaunchKernelGGL((mm_stream_tiles_kernel<ELEM_BF16, BATCH, TW>), grid, block, 0, st, g, g.rows, g.blks, pitems, g.scales);
 }
 
 hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg, hipStream_t st) {
@@ -1340,7 +1354,8 @@ hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg
              L.in_pts, L.init, L.out_tree, L.out_pts, L.Y, L.ldy, nullptr, nullptr, L.ncols};
     const int nt = mm_tile_width(cfg, L.ncols);
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
-    if (phase == PHASE_STREAM && nt == 16) launch_narrow<false>(g, kind, L.pitems, L.npitems, st);
+    if (phase == PHASE_STREAM && stream_by_tiles(nt, kind, false, L.npitems))
+        (nt == 16 ? launch_stream_tiles<false, 16> : launch_stream_tiles<false, 32>)(g, kind, L.pitems, L.npitems, st);
     else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<false, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
     else launch_phase<false, false>(g, kind, phase, nt, cfg.pipelined, unsigned(slots), st);
     return hipGetLastError();
@@ -1357,7 +1372,8 @@ hipError_t launch_mm_batch(const MmBatchLaunch &L, int kind, int phase, const Mm
     if (L.ncols < 1 || L.ncols > MM_TILE) return hipErrorInvalidValue;
     const int nt = mm_tile_width(cfg, L.ncols);
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
-    if (phase == PHASE_STREAM && nt == 16) launch_narrow<true>(g, kind, L.pitems, L.npitems, st);
+    if (phase == PHASE_STREAM && stream_by_tiles(nt, kind, true, L.npitems))
+        (nt == 16 ? launch_stream_tiles<true, 16> : launch_stream_tiles<true, 32>)(g, kind, L.pitems, L.npitems, st);
     else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<true, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
     else launch_phase<true, false>(g, kind, phase, nt, cfg.pipelined, unsigned(slots), st);
     return hipGetLastError();
@@ -1395,7 +1411,7 @@ __global__ __launch_bounds__(256) void batch_pack_kernel(const PackEntry *__rest
             }
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (j0 + u < nc) t[tile_width == 16 ? tile16(c, j0 + u) : (j0 + u) * mp + c] = c < e.m ? v[u] : 0.0f;
+                if (j0 + u < nc) t[tile_width == 16 ? tile_at<16>(c, j0 + u) : tile_at<32>(c, j0 + u)] = c < e.m ? v[u] : 0.0f;
         }
     }
 }

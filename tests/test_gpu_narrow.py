@@ -1,5 +1,5 @@
-"""Products with at most 16 right-hand sides at the edges of the streaming
-launch's shapes: rows of 1 to 4 tiles of 16, block widths that are no multiple
+"""Many right-hand sides at the edges of the streaming launch's shapes (16-wide
+tiles, and 32-wide ones in short lists): rows of 1 to 4 tiles of 16, block widths that are no multiple
 of a chunk (16 columns, BF16 32), rows without blocks of a wavefront's share,
 and rows whose share exceeds the 64 block descriptors loaded at a time (3-D,
 small leaves), against the oracle on the same dequantized values.
@@ -15,7 +15,8 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 CASES = [(2, 1, 300, 3, 2), (2, 4, 900, 16, 16), (2, 4, 1000, 17, 1), (2, 5, 2000, 33, 8), (2, 7, 3000, 50, 9),
-         (2, 8, 1500, 64, 16), (3, 3, 12000, 12, 3), (3, 2, 4000, 8, 5), (3, 4, 6000, 47, 15), (2, 3, 20, 64, 4)]
+         (2, 8, 1500, 64, 16), (3, 3, 12000, 12, 3), (3, 2, 4000, 8, 5), (3, 4, 6000, 47, 15), (2, 3, 20, 64, 4),
+         (2, 4, 900, 17, 17), (2, 7, 1500, 50, 32), (2, 8, 1000, 64, 20), (3, 2, 3000, 8, 31), (3, 3, 5000, 30, 40)]
 
 
 @pytest.mark.parametrize("storage", [1, 2], ids=["fp32", "bf16"])
