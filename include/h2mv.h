@@ -339,12 +339,11 @@ h2_status h2_set_schedule(h2_handle A, int schedule, int near_wg_per_cu, double 
  * the tiles (two per tree node and two per leaf); on an H2_FP64 handle a call
  * that finds no memory for them, or comes first while its stream is being
  * captured, runs single-vector products instead.  The first call on an H2_FP32
- * or H2_BF16_SCALED handle also times the candidate launch shapes (the block loop's
- * prefetch depth 0..7 as listed at h2_batch_tuning, one workgroup per item
- * group or a persistent grid of 1 or 2 workgroups per compute unit, and the
- * MFMA tile width 16 or 32 for passes of at most 16 right-hand sides) on its
- * first pass and keeps the
- * fastest (cached like a batch's choice, below; h2_matmat_tuning reports it).
+ * or H2_BF16_SCALED handle also times three launch shapes (the block loop's
+ * prefetch depth, as listed at h2_batch_tuning: 0, 2 and 6 with 16-wide tiles
+ * for passes of at most 16 right-hand sides, else 0, 4 and 5 with 32-wide
+ * ones) on its first pass and keeps the fastest (cached like a batch's choice,
+ * below; h2_matmat_tuning reports it).
  * Errors: INVALID_ARG for nrhs < 1, ldx < n, ldy < n, NULL pointers or a
  * structure-only handle; DEVICE. */
 h2_status h2_matmat(h2_handle A, const double *X, int64_t ldx, double *Y, int64_t ldy,
@@ -426,12 +425,14 @@ h2_status h2_batch_matmat(h2_batch B, const double *const *X, const int64_t *ldx
  * chunk; with 32-wide tiles also 4 or 5, a ring of 1 or 2 blocks with the
  * two 32-row halves of a row in one workgroup sharing each input tile
  * through LDS; with 16-wide tiles also 6 or 7, a ring of 6 or 8 column
- * chunks of 16 (FP32) or 32 (BF16) block columns, so that rows of narrow
+ * chunks of 16 block columns, so that rows of narrow
  * blocks keep more blocks in flight), grid
  * (workgroups; 0 = one per item group), tile_width (16: 16x16
  * MFMAs; 32: 32x32 MFMAs) and the tuned time in ms of one product (-1 before
  * the first product; 0 when the choice came from the cache or
- * h2_batch_set_tuning). */
+ * h2_batch_set_tuning).  The shape is that of the sweeps, and of the streaming
+ * launch of long lists with 32-wide tiles; 16-wide tiles, short lists and FP32
+ * batches stream in one way whatever the shape. */
 h2_status h2_batch_tuning(h2_batch B, int *pipelined, int64_t *grid, int *tile_width, double *tuned_ms);
 /* Fixes the configuration instead of timing the candidates: pipelined 0..7
  * (4 and 5 with tile_width 32 only, 6 and 7 with tile_width 16 only), grid >= 0, tile_width 16 (at most 16

@@ -223,7 +223,7 @@ struct MmConfig {
 inline int mm_tile_width(const MmConfig &cfg, int ncols) { return cfg.nt == 32 || ncols > 16 ? 32 : 16; }
 hipError_t launch_mm(const MmLaunch &L, int kind, int phase, const MmConfig &cfg, hipStream_t st);
 
-// ---- many right-hand sides, FP64 matrices (h2_mm64.hip)
+// ---- many right-hand sides, FP64 matrices (h2_mm64.h)
 // The same tile lists; tiles hold FP64 values, [row][rhs] with NR = 16 (at
 // most 16 right-hand sides in the pass) or 32 per row, rows padded to 16.
 struct Mm64Launch {
