@@ -1,6 +1,6 @@
 """Device memory that outlives a handle: matrices made and dropped in turn (the
 next ones get the memory of the last) give bitwise the products of the first,
-on several host threads at once, and nothing is held once all are gone."""
+on several host threads at once."""
 import threading
 
 import numpy as np
