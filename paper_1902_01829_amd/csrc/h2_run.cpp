@@ -265,6 +265,17 @@ void run_tiles64(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t
     }
 }
 
+// Calls of this thread that HIP refuses while another stream of the process is
+// being captured in global mode (and breaks that capture for) are let through:
+// an allocation is no part of anyone's capture.
+struct BesideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    BesideCaptures() { check_hip(hipThreadExchangeStreamCaptureMode(&mode), "hipThreadExchangeStreamCaptureMode"); }
+    ~BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+    BesideCaptures(const BesideCaptures &) = delete;
+    BesideCaptures &operator=(const BesideCaptures &) = delete;
+};
+
 // Whether the FP64 tile workspace is there, allocated now if it can be: not
 // while the stream is being captured, and not when memory is short (the
 // product then runs column by column, in the handle's own workspace).
@@ -273,6 +284,7 @@ bool tiles64_ready(h2_matrix_ &A, hipStream_t st) {
     hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
     check_hip(hipStreamIsCapturing(st, &capture), "hipStreamIsCapturing");
     if (capture != hipStreamCaptureStatusNone) return false;
+    const BesideCaptures beside;
     try {
         ensure_tiles(A);
     } catch (const Failure &f) {
