@@ -93,6 +93,12 @@ struct DevicePool {
         held += nbytes;
         return true;
     }
+    int64_t held_on(int device) {
+        std::lock_guard<std::mutex> g(m);
+        int64_t sum = 0;
+        for (const Block &b : blocks) sum += b.device == device ? b.bytes : 0;
+        return sum;
+    }
     void clear() {
         std::vector<Block> old;
         {

@@ -39,14 +39,22 @@ void run_lists(h2_matrix_ &A, const std::vector<WorkList> &lists, hipStream_t st
     }
 }
 
-// Tile workspace of the many-right-hand-side product, allocated at first use
-// (one allocation: none of it stays behind when memory runs out).
-void ensure_tiles(h2_matrix_ &A) {
-    if (A.t_xh) return;
+// Bytes of the tile workspace of the many-right-hand-side product, those of
+// its tree and point parts (two of each).
+int64_t tile_bytes(const h2_matrix_ &A, int64_t &tree, int64_t &pts) {
     const int64_t vb = A.vec_f64 ? 8 : 4, kp = (A.st.rank + 15) / 16 * 16;
     auto r256 = [](int64_t b) { return (b + 255) / 256 * 256; };
-    const int64_t tree = r256(A.st.nnodes * kp * h2::MM_TILE * vb);
-    const int64_t pts = r256((int64_t(1) << A.st.q) * A.tile_slot * vb);
+    tree = r256(A.st.nnodes * kp * h2::MM_TILE * vb);
+    pts = r256((int64_t(1) << A.st.q) * A.tile_slot * vb);
+    return 2 * (tree + pts);
+}
+
+// The workspace, allocated at first use (one allocation: none of it stays
+// behind when memory runs out).
+void ensure_tiles(h2_matrix_ &A) {
+    if (A.t_xh) return;
+    int64_t tree = 0, pts = 0;
+    tile_bytes(A, tree, pts);
     char *p = static_cast<char *>(A.mem.alloc(2 * tree + 2 * pts));
     A.t_xh = p;
     A.t_yh = p + tree;
@@ -285,6 +293,17 @@ bool tiles64_ready(h2_matrix_ &A, hipStream_t st) {
     check_hip(hipStreamIsCapturing(st, &capture), "hipStreamIsCapturing");
     if (capture != hipStreamCaptureStatusNone) return false;
     const BesideCaptures beside;
+    // Where the device cannot have the memory, it is not asked: a refused
+    // allocation costs a wait for the device and what is kept for the next
+    // handles, and this call comes back with every product.  (A sixteenth more,
+    // for what the runtime rounds up.)
+    int64_t tree = 0, pts = 0;
+    const int64_t need = tile_bytes(A, tree, pts);
+    int device = 0;
+    size_t free_bytes = 0, total = 0;
+    check_hip(hipGetDevice(&device), "hipGetDevice");
+    check_hip(hipMemGetInfo(&free_bytes, &total), "hipMemGetInfo");
+    if (int64_t(free_bytes) + DevicePool::get().held_on(device) < need + need / 16) return false;
     try {
         ensure_tiles(A);
     } catch (const Failure &f) {

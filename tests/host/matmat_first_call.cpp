@@ -19,6 +19,32 @@ int main(int, char **argv) {
         CHECK(!fake::capture_broken && fake::mode == hipStreamCaptureModeGlobal);
         CHECK(fake::tile_launches == 1 && fake::single_products == 0);
         fake::other_capture = false;
+    } else if (what == "no_memory") {
+        // too little memory, most of what is there kept for the next handle: single products,
+        // without a try at the device and without giving up what is kept, call after call
+        h2_matrix_ *B = fake::matrix(6, H2_FP64);
+        B->mem.alloc(4096);
+        B->mem.alloc(1 << 20);
+        delete B;
+        fake::budget = fake::used + (1 << 20);
+        const int64_t used = fake::used;
+        const int mallocs = fake::mallocs, frees = fake::frees;
+        for (int k = 1; k <= 3; ++k) {
+            CHECK(product() == H2_OK);
+            CHECK(fake::single_products == 4 * k && fake::tile_launches == 0);
+        }
+        CHECK(fake::mallocs == mallocs && fake::frees == frees && fake::used == used);
+        // memory comes back: tiles again
+        fake::budget = int64_t(1) << 40;
+        CHECK(product() == H2_OK && fake::single_products == 12 && fake::tile_launches == 1);
+    } else if (what == "memory_kept") {
+        // enough memory once what is kept for the next handle is given back
+        h2_matrix_ *B = fake::matrix(6, H2_FP64);
+        B->mem.alloc(4096);
+        for (int k = 0; k < 8; ++k) B->mem.alloc(8 << 20);
+        delete B;
+        fake::budget = fake::used + (1 << 20);
+        CHECK(product() == H2_OK && fake::single_products == 0 && fake::tile_launches == 1);
     }
     delete A;
     return 0;

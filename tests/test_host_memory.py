@@ -37,3 +37,11 @@ def first_call(tmp_path_factory):
 
 def test_first_fp64_columns_beside_another_streams_capture(first_call):
     _check(first_call, "beside_a_capture")
+
+
+def test_fp64_columns_without_memory_for_tiles(first_call):
+    _check(first_call, "no_memory")
+
+
+def test_fp64_columns_take_the_memory_kept_for_later(first_call):
+    _check(first_call, "memory_kept")
