@@ -48,8 +48,10 @@ inline void check_hip(hipError_t e, const char *where) {
 // that builds, compresses or transposes in a loop asks for the same sizes
 // again (a matrix of 40,000 points transposed after others had come and gone:
 // 4.6 -> 0.8 ms).  Holds at most kLimit bytes in blocks of at least kLeast,
-// and none once the process has no matrix or batch left.  Blocks come here
-// only after a wait for their device, so any stream may use them next.
+// and none once the process has no matrix or batch left.  A block serves
+// requests of exactly its size, so that what an owner counts is what it holds.
+// Blocks come here only after a wait for their device, so any stream may use
+// them next.
 struct DevicePool {
     static constexpr int64_t kLimit = int64_t(1) << 30, kLeast = 64 << 10;
     struct Block {
@@ -66,20 +68,17 @@ struct DevicePool {
         static DevicePool *pool = new DevicePool;   // never destroyed: the HIP runtime may be gone first
         return *pool;
     }
-    // A block of nbytes to nbytes * 5/4 (its size in got), or null.
-    void *take(int device, int64_t nbytes, int64_t &got) {
+    // A block of nbytes, or null.
+    void *take(int device, int64_t nbytes) {
         std::lock_guard<std::mutex> g(m);
-        size_t best = blocks.size();
-        for (size_t i = 0; i < blocks.size(); ++i)
-            if (blocks[i].device == device && blocks[i].bytes >= nbytes && blocks[i].bytes <= nbytes + nbytes / 4 &&
-                (best == blocks.size() || blocks[i].bytes < blocks[best].bytes))
-                best = i;
-        if (best == blocks.size()) return nullptr;
-        void *p = blocks[best].p;
-        got = blocks[best].bytes;
-        held -= got;
-        blocks.erase(blocks.begin() + long(best));
-        return p;
+        for (size_t i = blocks.size(); i-- > 0;)
+            if (blocks[i].device == device && blocks[i].bytes == nbytes) {
+                void *p = blocks[i].p;
+                held -= nbytes;
+                blocks.erase(blocks.begin() + long(i));
+                return p;
+            }
+        return nullptr;
     }
     // False: not kept, the caller frees it.
     bool give(int device, int64_t nbytes, void *p) {
@@ -174,11 +173,10 @@ struct DeviceArena {
     void *device_malloc(int64_t nbytes) {   // not counted
         int device = 0;
         check_hip(hipGetDevice(&device), "hipGetDevice");
-        int64_t got = nbytes;
         ptrs.reserve(ptrs.size() + 1);
-        void *p = nbytes >= DevicePool::kLeast ? DevicePool::get().take(device, nbytes, got) : nullptr;
+        void *p = nbytes >= DevicePool::kLeast ? DevicePool::get().take(device, nbytes) : nullptr;
         if (p) {
-            ptrs.push_back({device, got, p});
+            ptrs.push_back({device, nbytes, p});
             return p;
         }
         hipError_t e = hipMalloc(&p, size_t(nbytes));

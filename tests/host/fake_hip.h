@@ -115,6 +115,7 @@ hipError_t launch_pack64(const double *, int64_t, int, const int64_t *, const in
                          hipStream_t) {
     return hipSuccess;
 }
+hipError_t launch_read_probe(const void *, int64_t, int, void *, hipStream_t) { return hipSuccess; }
 hipError_t launch_mm64(const Mm64Launch &, int, hipStream_t) { return ++fake::tile_launches, hipSuccess; }
 
 }  // namespace h2

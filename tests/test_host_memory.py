@@ -1,5 +1,5 @@
 """Device memory as the library's host code handles it -- the tile workspace
-made by a first product -- compiled with g++ against a HIP runtime that only
+made by a first product, and what is kept for later calls -- compiled with g++ against a HIP runtime that only
 keeps count (tests/host/fake_hip.h); no GPU."""
 import os
 import shutil
@@ -45,3 +45,12 @@ def test_fp64_columns_without_memory_for_tiles(first_call):
 
 def test_fp64_columns_take_the_memory_kept_for_later(first_call):
     _check(first_call, "memory_kept")
+
+
+@pytest.fixture(scope="module")
+def kept(tmp_path_factory):
+    return _program(tmp_path_factory.mktemp("host"), "kept_memory", ["h2_api.cpp"])
+
+
+def test_kept_memory_serves_its_own_size(kept):
+    _check(kept, "sizes")
