@@ -20,7 +20,8 @@
  *  - Pointers.  "host" pointers are read or written before the call returns;
  *    "device" pointers are HIP device memory owned by the caller.  Input host
  *    arrays are copied; the handle owns all device memory it allocates (the
- *    representation and its workspace) until h2_free.
+ *    representation and its workspace) until h2_free.  Device memory that calls
+ *    have given up may be kept for later ones: see h2_release_kept.
  *  - Streams.  Every device operation is enqueued on the given hipStream_t
  *    (NULL = default stream) and is asynchronous.  A handle's workspace is shared
  *    by its calls: do not run two calls on one handle concurrently.
@@ -363,6 +364,15 @@ h2_status h2_matmat_set_tuning(h2_handle A, int narrow, int pipelined, int64_t g
 /* Release every device and host resource of A.  NULL is a no-op.  The caller
  * must make sure no enqueued work on A is still running. */
 void h2_free(h2_handle A);
+
+/* Give the device memory kept for later calls back to the device.  Of what
+ * h2_free, h2_batch_free and the scratch of set-up calls give up, the process
+ * keeps at most 256 MiB, and only while it has a matrix or a batch and more
+ * than a sixteenth of the device's memory is free; none of it belongs to a
+ * handle or is counted in bytes_device_total, and a device allocation of this
+ * library that fails returns it and tries again.  May be called at any time,
+ * from any thread; hipFree waits for the device's work. */
+void h2_release_kept(void);
 
 /* Sizes and byte counts of A (host struct). */
 h2_status h2_get_info(h2_handle A, h2_info *info);

@@ -18,6 +18,8 @@ const char *h2_last_error(void) { return g_last_error.c_str(); }
 
 void h2_free(h2_handle A) { delete A; }
 
+void h2_release_kept(void) { DevicePool::get().clear(); }
+
 h2_status h2_get_info(h2_handle A, h2_info *info) {
     if (!A || !info) {
         g_last_error = "NULL argument";

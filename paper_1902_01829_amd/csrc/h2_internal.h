@@ -48,19 +48,20 @@ inline void check_hip(hipError_t e, const char *where) {
 // that builds, compresses or transposes in a loop asks for the same sizes
 // again (a matrix of 40,000 points transposed after others had come and gone:
 // 4.6 -> 0.8 ms).  Holds at most kLimit bytes in blocks of at least kLeast,
-// and none once the process has no matrix or batch left.  A block serves
-// requests of exactly its size, so that what an owner counts is what it holds.
-// Blocks come here only after a wait for their device, so any stream may use
-// them next.
+// the latest ones; none while less than 1 / kShare of the device's memory is
+// free, nor once the process has no matrix or batch left, nor after
+// h2_release_kept.  A block serves requests of exactly its size, so that what
+// an owner counts is what it holds.  Blocks come here only after a wait for
+// their device, so any stream may use them next.
 struct DevicePool {
-    static constexpr int64_t kLimit = int64_t(1) << 30, kLeast = 64 << 10;
+    static constexpr int64_t kLimit = int64_t(256) << 20, kLeast = 64 << 10, kShare = 16;
     struct Block {
         int device;
         int64_t bytes;
         void *p;
     };
     std::mutex m;
-    std::vector<Block> blocks;
+    std::vector<Block> blocks;   // oldest first
     int64_t held = 0;
     int live = 0;   // matrices and batches
 
@@ -81,15 +82,24 @@ struct DevicePool {
         return nullptr;
     }
     // False: not kept, the caller frees it.
-    bool give(int device, int64_t nbytes, void *p) {
-        std::lock_guard<std::mutex> g(m);
-        if (live == 0 || nbytes < kLeast || held + nbytes > kLimit) return false;
-        try {
-            blocks.push_back({device, nbytes, p});
-        } catch (const std::bad_alloc &) {
-            return false;
+    bool give(const Block &b) {
+        std::vector<Block> old;   // what makes room for it
+        {
+            std::lock_guard<std::mutex> g(m);
+            if (live == 0 || b.bytes < kLeast || b.bytes > kLimit) return false;
+            try {
+                size_t n = 0;
+                for (int64_t sum = held + b.bytes; sum > kLimit; ++n) sum -= blocks[n].bytes;
+                old.assign(blocks.begin(), blocks.begin() + long(n));
+                blocks.push_back(b);
+            } catch (const std::bad_alloc &) {
+                return false;
+            }
+            blocks.erase(blocks.begin(), blocks.begin() + long(old.size()));
+            held += b.bytes;
+            for (const Block &o : old) held -= o.bytes;
         }
-        held += nbytes;
+        for (const Block &o : old) (void)hipFree(o.p);
         return true;
     }
     int64_t held_on(int device) {
@@ -200,11 +210,15 @@ struct DeviceArena {
         std::swap(*std::min_element(ptrs.begin(), ptrs.end(),
                                     [](const DevicePool::Block &x, const DevicePool::Block &y) { return x.bytes < y.bytes; }),
                   ptrs.front());
-        const bool idle = hipFree(ptrs.front().p) == hipSuccess;
+        bool keep = hipFree(ptrs.front().p) == hipSuccess;
+        size_t free_bytes = 0, total = 0;
+        if (keep && hipMemGetInfo(&free_bytes, &total) == hipSuccess && free_bytes < total / DevicePool::kShare) {
+            keep = false;
+            DevicePool::get().clear();
+        }
         for (size_t i = 1; i < ptrs.size(); ++i) {
             const DevicePool::Block &b = ptrs[i];
-            if (!idle || b.device != ptrs.front().device || !DevicePool::get().give(b.device, b.bytes, b.p))
-                (void)hipFree(b.p);
+            if (!keep || b.device != ptrs.front().device || !DevicePool::get().give(b)) (void)hipFree(b.p);
         }
         ptrs.clear();
     }

@@ -26,7 +26,7 @@ H2_SCHEDULE_MERGED, H2_SCHEDULE_STREAMED = 0, 1
 EXPORTS = ("h2_build_from_points", "h2_build_from_arrays", "h2_export_arrays", "h2_orthogonalize", "h2_compress", "h2_transpose", "h2_matvec", "h2_matvec_noalloc", "h2_matmat", "h2_free", "h2_get_info", "h2_get_perm",
            "h2_get_level_bsr", "h2_profile", "h2_profile_read", "h2_batch_create", "h2_batch_matmat",
            "h2_batch_tuning", "h2_batch_set_tuning", "h2_matmat_tuning", "h2_matmat_set_tuning", "h2_batch_free", "h2_read_probe", "h2_set_schedule",
-           "h2_last_error")
+           "h2_release_kept", "h2_last_error")
 
 
 class h2_params(C.Structure):
@@ -89,6 +89,8 @@ def lib():
         L.h2_matmat.argtypes = [vp, vp, i64, vp, i64, C.c_int, vp]
         L.h2_free.argtypes = [vp]
         L.h2_free.restype = None
+        L.h2_release_kept.argtypes = []
+        L.h2_release_kept.restype = None
         L.h2_get_info.argtypes = [vp, C.POINTER(h2_info)]
         L.h2_get_perm.argtypes = [vp, vp]
         L.h2_get_level_bsr.argtypes = [vp, C.c_int, C.POINTER(i64), vp, vp]
@@ -108,7 +110,7 @@ def lib():
         L.h2_last_error.argtypes = []
         L.h2_last_error.restype = C.c_char_p
         for name in EXPORTS:
-            if name not in ("h2_free", "h2_batch_free", "h2_last_error"):
+            if name not in ("h2_free", "h2_batch_free", "h2_release_kept", "h2_last_error"):
                 getattr(L, name).restype = C.c_int
         _lib = L
     return _lib
@@ -241,6 +243,11 @@ def h2_matmat(h, X_ptr, ldx, Y_ptr, ldy, nrhs, stream=0):
 
 def h2_free(h):
     lib().h2_free(C.c_void_p(h))
+
+
+def h2_release_kept():
+    """Gives device memory kept for later calls back to the device (h2mv.h)."""
+    lib().h2_release_kept()
 
 
 def h2_get_info(h) -> h2_info:

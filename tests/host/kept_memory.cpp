@@ -6,14 +6,47 @@ using h2i::DeviceArena;
 
 int main(int, char **argv) {
     const std::string what = argv[1];
-    constexpr int64_t MiB = 1 << 20;
+    constexpr int64_t MiB = 1 << 20, bound = 256 * MiB;
     h2_matrix_ *A = fake::matrix(2, H2_FP64), *B = fake::matrix(2, H2_FP64);
     auto dropped = [](int blocks, int64_t bytes) {   // an owner of so many blocks that comes and goes
         DeviceArena a;
         a.alloc(256);
         for (int k = 0; k < blocks; ++k) a.alloc(bytes);
     };
-    if (what == "sizes") {
+    if (what == "bound") {
+        for (int k = 0; k < 5; ++k) dropped(12, 24 * MiB);
+        CHECK(fake::used <= bound);
+        dropped(2, 2 * bound);
+        CHECK(fake::used <= bound);
+        // the latest blocks are the ones kept: a program that moves on to other sizes finds these
+        dropped(4, 16 * MiB);
+        const int mallocs = fake::mallocs;
+        dropped(4, 16 * MiB);
+        CHECK(fake::mallocs == mallocs + 1 && fake::used <= bound);
+    } else if (what == "given_back") {
+        dropped(4, 16 * MiB);
+        CHECK(fake::used > 0);
+        h2_free(A);
+        CHECK(fake::used > 0);
+        h2_free(B);   // the last handle
+        CHECK(fake::used == 0 && fake::blocks.empty());
+        return 0;
+    } else if (what == "release") {
+        dropped(4, 16 * MiB);
+        CHECK(fake::used > 0);
+        h2_release_kept();
+        CHECK(fake::used == 0 && fake::blocks.empty());
+        dropped(4, 16 * MiB);   // kept again
+        CHECK(fake::used > 0);
+    } else if (what == "short_memory") {
+        // less than a sixteenth of the device free: nothing is kept, and nothing stays kept
+        dropped(4, 16 * MiB);
+        DeviceArena other;
+        fake::budget = 1600 * MiB;
+        other.alloc(1480 * MiB);
+        dropped(1, 2 * MiB);
+        CHECK(fake::used == other.bytes);
+    } else if (what == "sizes") {
         // an owner holds no more than it counts
         dropped(2, 20 * MiB);
         DeviceArena a;

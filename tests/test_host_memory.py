@@ -54,3 +54,10 @@ def kept(tmp_path_factory):
 
 def test_kept_memory_serves_its_own_size(kept):
     _check(kept, "sizes")
+
+
+@pytest.mark.parametrize("what", ["bound", "given_back", "release", "short_memory"])
+def test_memory_kept_for_later_calls(kept, what):
+    """At most 256 MiB, the latest blocks; all given back with the last handle,
+    on request, and where the device is short of memory."""
+    _check(kept, what)
