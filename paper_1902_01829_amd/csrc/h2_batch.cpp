@@ -32,6 +32,11 @@ std::string config_file() {
     return p ? std::string(p) : std::string();
 }
 
+// First part of every signature: the kernels and candidates that the choices
+// were timed with.  Another one whenever these change, so that choices saved
+// before are timed again and not obeyed.
+constexpr const char *kTuned = "s2-";
+
 // The cache file holds one "signature pipelined grid tile_width" line per
 // entry (a line without the tile width means 0: chosen by the pass width).
 bool cached_config(const std::string &sig, h2::MmConfig &cfg) {
@@ -268,7 +273,7 @@ void build_batch(h2_batch_ &B, hipStream_t stream) {
     check_hip(hipGetDevice(&dev), "hipGetDevice");
     check_hip(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device attribute");
     B.cu_count = cus;
-    B.signature = "batch-k" + std::to_string(kind_block) + "-r" + std::to_string(B.nrhs) + "-m" + std::to_string(nm) +
+    B.signature = kTuned + std::string("batch-k") + std::to_string(kind_block) + "-r" + std::to_string(B.nrhs) + "-m" + std::to_string(nm) +
                   "-rows" + std::to_string(total_rows) + "-blocks" + std::to_string(total_blocks) + "-cu" +
                   std::to_string(cus);
     check_hip(hipStreamCreateWithFlags(&B.own, hipStreamNonBlocking), "hipStreamCreate");
@@ -288,9 +293,12 @@ void tune_tiles(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64_t 
     const int w = ncols <= 16 ? 1 : 0;
     int64_t nblocks = 0;
     for (const auto &hb : A.mm_host_blks) nblocks += int64_t(hb.size());
-    const std::string sig = "single-k" + std::to_string(A.block_kind) + "-n" + std::to_string(A.st.n) + "-r" +
-                            std::to_string(A.st.rank) + "-blocks" + std::to_string(nblocks) + "-nt" +
-                            std::to_string(w ? 16 : 32);
+    int dev = 0, cus = 256;
+    check_hip(hipGetDevice(&dev), "hipGetDevice");
+    check_hip(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev), "device attribute");
+    const std::string sig = kTuned + std::string("single-k") + std::to_string(A.block_kind) + "-n" +
+                            std::to_string(A.st.n) + "-r" + std::to_string(A.st.rank) + "-blocks" +
+                            std::to_string(nblocks) + "-nt" + std::to_string(w ? 16 : 32) + "-cu" + std::to_string(cus);
     h2::MmConfig best{1, 0, 0};
     double best_ms = 0.0;
     if (!cached_config(sig, best)) {
