@@ -315,13 +315,18 @@ __global__ __launch_bounds__(256) void pack64_kernel(const double *__restrict__ 
 // rows less to drain.
 constexpr int kDepth = 4;
 
-// Lists of at most this many items (wavefronts) run four wavefronts per item:
-// too few to fill the chip, each a chain of up to some hundred chunks.  One
-// against four wavefronts per item: 4,096 2-D points, 32 right-hand sides
-// 87 -> 59 us; 6,000 points of rank 64 166 -> 118 us; 30,000 points 339 ->
-// 320 us; above the line it loses to its extra barrier and sums (60,000
-// points, 33 right-hand sides 1.22 -> 1.43 ms; 2^18 points 2.8 -> 3.6 ms).
-constexpr int64_t kSplitItems = 8192;
+// Launches of at most this many items (wavefronts; a list's padding counts) run
+// four wavefronts per item: too few to fill the chip, each a chain of up to
+// some hundred chunks.  Above the line the extra barrier and sums cost more.
+// 32 right-hand sides, whole products, one / four wavefronts per item of the
+// streaming launch: 3-D, rank 64, 15,000 points (4,096 items) 567 / 459 us, 30,000
+// (6,528) 1250 / 1042; 2-D, rank 49, 15,000 (2,464) 260 / 204, 30,000 (4,512)
+// 380 / 397 (8 right-hand sides 311 / 301); rank 25, 60,000 (8,000) 408 / 446;
+// stored by halves the same within 4 %.  Sweep launches have at most a few
+// blocks per item; four wavefronts up to 8,192 / 1,024 / 512 items: 2-D, 2^18
+// points 2.90 / 2.78 / 2.76 ms, 100,000 of rank 36 1342 / 1141 / 1129 us, 60,000 of
+// rank 49 710 / 678 / 668; up to 256 / none: 8,000 points of rank 64 125 / 140 us.
+constexpr int64_t kSplitStream = 7168, kSplitSweep = 512;
 
 template <int NR, int SPLIT>
 void launch_phase64(const Mm64Launch &L, int phase, hipStream_t st) {
@@ -343,7 +348,7 @@ void launch_phase64(const Mm64Launch &L, int phase, hipStream_t st) {
 hipError_t launch_mm64(const Mm64Launch &L, int phase, hipStream_t st) {
     if (L.nitems <= 0) return hipSuccess;
     if (L.nitems % 4 != 0 || L.ncols < 1 || L.ncols > MM_TILE) return hipErrorInvalidValue;
-    const bool split = L.nitems <= kSplitItems;
+    const bool split = L.nitems <= (phase == PHASE_STREAM ? kSplitStream : kSplitSweep);
     if (L.ncols > 16) split ? launch_phase64<32, 4>(L, phase, st) : launch_phase64<32, 1>(L, phase, st);
     else split ? launch_phase64<16, 4>(L, phase, st) : launch_phase64<16, 1>(L, phase, st);
     return hipGetLastError();
