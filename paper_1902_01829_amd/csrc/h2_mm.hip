@@ -1287,12 +1287,15 @@ static void launch_phase_nt(const MmArgs &g, int kind, int phase, unsigned grid,
     case PHASE_LEAF:
         hipLaunchKernelGGL((mm_leafexpand_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
         break;
-    default:   // (16-wide: launch_stream_tiles)
+    default:   // (16-wide tiles and FP32 batches: launch_stream_tiles, see stream_by_tiles)
         if constexpr (NT == 32) {
-            if (kind == ELEM_F32)
-                hipLaunchKernelGGL((mm_stream_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
-            else
-                hipLaunchKernelGGL((mm_stream_kernel<ELEM_BF16, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
+            if constexpr (!BATCH) {
+                if (kind == ELEM_F32) {
+                    hipLaunchKernelGGL((mm_stream_kernel<ELEM_F32, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
+                    break;
+                }
+            }
+            hipLaunchKernelGGL((mm_stream_kernel<ELEM_BF16, BATCH, PIPE, PERSIST, NT>), gd, bd, 0, st, g, g.rows, g.blks, g.items, g.scales);
         }
     }
 }
@@ -1372,7 +1375,9 @@ hipError_t launch_mm_batch(const MmBatchLaunch &L, int kind, int phase, const Mm
     if (L.ncols < 1 || L.ncols > MM_TILE) return hipErrorInvalidValue;
     const int nt = mm_tile_width(cfg, L.ncols);
     const int64_t slots = pair ? L.npitems / 2 : L.nitems / 4;
-    if (phase == PHASE_STREAM && stream_by_tiles(nt, kind, true, L.npitems))
+    const bool tiles = phase == PHASE_STREAM && stream_by_tiles(nt, kind, true, L.npitems);
+    if (phase == PHASE_STREAM && kind == ELEM_F32 && !tiles) return hipErrorInvalidValue;   // no such loops are built
+    if (tiles)
         (nt == 16 ? launch_stream_tiles<true, 16> : launch_stream_tiles<true, 32>)(g, kind, L.pitems, L.npitems, st);
     else if (cfg.grid > 0 && cfg.grid < slots) launch_phase<true, true>(g, kind, phase, nt, cfg.pipelined, unsigned(cfg.grid), st);
     else launch_phase<true, false>(g, kind, phase, nt, cfg.pipelined, unsigned(slots), st);
