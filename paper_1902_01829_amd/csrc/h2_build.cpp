@@ -546,7 +546,7 @@ void build_lists(h2_matrix_ &A, const std::vector<h2::FillDesc> &fill, int64_t n
             w.npitems = int64_t(e.pitems.size());
         }
         (enc == 0 ? A.lists : A.mm_lists).push_back(w);
-        if (enc == 1) {
+        if (enc == 1 && !A.vec_f64 && !A.half) {   // batches take no others
             A.mm_host_rows.push_back(std::move(e.rows));
             A.mm_host_blks.push_back(std::move(e.blks));
         }

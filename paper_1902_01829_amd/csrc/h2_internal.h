@@ -362,7 +362,7 @@ struct h2_matrix_ {
     int64_t *d_off_U = nullptr, *d_off_VT = nullptr, *d_off_E = nullptr, *d_off_FT = nullptr;   // off_* on the device
     h2::SumRange *d_tree_sums = nullptr, *d_near_sums = nullptr;   // cut streaming list: chunks per node / leaf
     std::vector<h2i::WorkList> mm_lists;   // tiles of MM_TILE right-hand sides (tile offsets)
-    std::vector<std::vector<h2::RowDesc>> mm_host_rows;   // host copies of mm_lists (for batches)
+    std::vector<std::vector<h2::RowDesc>> mm_host_rows;   // host copies of mm_lists (of matrices that batches take)
     std::vector<std::vector<h2::BlkDesc>> mm_host_blks;
     int64_t nscales = 0;
     int64_t tile_slot = 0;            // elements per leaf in point tiles
