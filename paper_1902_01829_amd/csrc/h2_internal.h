@@ -47,22 +47,28 @@ inline void check_hip(hipError_t e, const char *where) {
 // large block takes ~0.3 ms, and up to 10 ms where a program frees often; one
 // that builds, compresses or transposes in a loop asks for the same sizes
 // again (a matrix of 40,000 points transposed after others had come and gone:
-// 4.6 -> 0.8 ms).  Holds at most kLimit bytes in blocks of at least kLeast,
-// the latest ones; none while less than 1 / kShare of the device's memory is
+// 4.6 -> 0.8 ms).  Holds at most kLimit bytes in blocks of at least kLeast;
+// one that finds no room drives out those nothing asked for while kStale others
+// came.  None is held while less than 1 / kShare of the device's memory is
 // free, nor once the process has no matrix or batch left, nor after
-// h2_release_kept.  A block serves requests of exactly its size, so that what
-// an owner counts is what it holds.  Blocks come here only after a wait for
+// h2_release_kept.  (65,536 points compressed in a loop, which asks for 260 MB
+// in blocks of up to 200 MB beside ones of 1.0 and 2.4 GB: 28.2 ms with 512 MiB,
+// 30.1 with 256 MiB, 28.9 with 1 GiB, where the block of 1.0 GB takes the room.)
+// A block serves requests of exactly its size, so that what an owner counts is
+// what it holds.  Blocks come here only after a wait for
 // their device, so any stream may use them next.
 struct DevicePool {
-    static constexpr int64_t kLimit = int64_t(256) << 20, kLeast = 64 << 10, kShare = 16;
+    static constexpr int64_t kLimit = int64_t(512) << 20, kLeast = 64 << 10, kShare = 16;
+    static constexpr int64_t kStale = 256;
     struct Block {
         int device;
         int64_t bytes;
         void *p;
+        int64_t since = 0;   // gives when it came here
     };
     std::mutex m;
     std::vector<Block> blocks;   // oldest first
-    int64_t held = 0;
+    int64_t held = 0, gives = 0;
     int live = 0;   // matrices and batches
 
     static DevicePool &get() {
@@ -86,15 +92,19 @@ struct DevicePool {
         std::vector<Block> old;   // what makes room for it
         {
             std::lock_guard<std::mutex> g(m);
-            if (live == 0 || b.bytes < kLeast || b.bytes > kLimit) return false;
+            ++gives;
+            if (live == 0 || b.bytes < kLeast) return false;
             try {
                 size_t n = 0;
-                for (int64_t sum = held + b.bytes; sum > kLimit; ++n) sum -= blocks[n].bytes;
+                int64_t sum = held + b.bytes;
+                for (; sum > kLimit && n < blocks.size() && gives - blocks[n].since > kStale; ++n) sum -= blocks[n].bytes;
+                if (sum > kLimit) return false;
                 old.assign(blocks.begin(), blocks.begin() + long(n));
                 blocks.push_back(b);
             } catch (const std::bad_alloc &) {
                 return false;
             }
+            blocks.back().since = gives;
             blocks.erase(blocks.begin(), blocks.begin() + long(old.size()));
             held += b.bytes;
             for (const Block &o : old) held -= o.bytes;
