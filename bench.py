@@ -546,14 +546,15 @@ def storage_modes(steps, warmup, nleaves=16):
 
 
 def matmat_modes(steps, warmup, fp64_matvec_ms, nleaves=8):
-    """The 2^20-point 2-D workload with 32 right-hand sides on the matrix cores,
-    FP32 and BF16 storage, against 32 single-vector FP64 products."""
+    """The 2^20-point 2-D workload with 32 right-hand sides on the matrix cores in
+    the three storages, against 32 single-vector FP64 products and the FP64
+    columns."""
     import torch
     from paper_1902_01829_amd import h2mv
     w = W.C4
     out = {"workload": w.name, "nrhs": w.nrhs,
            "fp64_32_matvecs_ms": None if fp64_matvec_ms is None else round(32 * fp64_matvec_ms, 3)}
-    for name in ("fp32", "bf16"):
+    for name in ("fp64", "fp32", "bf16"):
         A = h2mv.H2Matrix(W.points(w), w.dim, w.leaf, w.cheb_p, w.eta, w.corr_len, storage=STORAGE[name])
         info, perm = A.info, A.perm()
         Xt = np.ascontiguousarray(W.rhs(w).T[:, perm])
@@ -570,14 +571,14 @@ def matmat_modes(steps, warmup, fp64_matvec_ms, nleaves=8):
         ms = (time.perf_counter() - t0) * 1e3 / steps
         phase_ms, calls = h2mv.h2_profile_read(A.handle)
         h2mv.h2_profile(A.handle, False)
-        tuning = A.matmat_tuning(0)
+        tuning = None if name == "fp64" else A.matmat_tuning(0)   # (FP64 passes run one shape)
         Yh = Y.cpu().numpy()
         A.close()
         del X, Y
         torch.cuda.empty_cache()
         nbytes = algorithmic_bytes(info, w.n, w.nrhs)
         entries = (info.bytes_coupling + info.bytes_dense + info.bytes_leaf_bases + info.bytes_transfers) / \
-            (4 if name == "fp32" else 1)
+            {"fp64": 8, "fp32": 4, "bf16": 1}[name]
         if name == "bf16":   # blocks are 2 bytes (+4 per block scale), bases 4 bytes
             entries = (info.bytes_coupling - 4 * info.coupling_blocks + info.bytes_dense - 4 * info.dense_blocks) / 2 \
                 + (info.bytes_leaf_bases + info.bytes_transfers) / 4
@@ -588,7 +589,7 @@ def matmat_modes(steps, warmup, fp64_matvec_ms, nleaves=8):
             errs.append(float(np.linalg.norm(Yh[j][rows] - ref) / np.linalg.norm(ref)))
         # roof = min(matrix-core peak, intensity x HBM peak); the useful products of BF16 blocks
         # are issued as three exact BF16 MFMAs each, so their matrix-core roof is 1/3 of the BF16 peak
-        peak = 157.3 if name == "fp32" else 2500.0 / 3
+        peak = {"fp64": 78.6, "fp32": 157.3, "bf16": 2500.0 / 3}[name]
         roof = min(peak, flops / nbytes * HBM_PEAK_GBS / 1e3)
         tflops = flops / (ms * 1e-3) / 1e12
         out[name] = {"ms": round(ms, 4), "GB_per_s": round(nbytes / (ms * 1e-3) / 1e9, 1),
@@ -597,6 +598,7 @@ def matmat_modes(steps, warmup, fp64_matvec_ms, nleaves=8):
                      "flops": flops, "stream_ms": round(float(phase_ms[1] / max(calls, 1)), 4),
                      "speedup_vs_32_fp64_matvecs": None if fp64_matvec_ms is None
                      else round(32 * fp64_matvec_ms / ms, 2),
+                     "speedup_vs_fp64_columns": round(out["fp64"]["ms"] / ms, 2) if "fp64" in out else 1.0,
                      "rel_err_vs_fp64_oracle_max": max(errs), "tuning": tuning}
         log(f"{w.name} matmat {name}: {ms:.3f} ms, {out[name]['GB_per_s']} GB/s, "
             f"{out[name]['TFLOP_per_s']} TFLOP/s, rel err {max(errs):.2e}, tuning {tuning}")

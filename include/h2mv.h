@@ -337,9 +337,11 @@ h2_status h2_set_schedule(h2_handle A, int schedule, int near_wg_per_cu, double 
  * side on H2_FP64 handles, run nrhs single-vector products; the others run on the matrix cores,
  * 32 right-hand sides per pass (FP64 MFMA and FP64 sums for H2_FP64, FP32 MFMA
  * for H2_FP32 and H2_BF16_SCALED).  The first such call on a handle allocates
- * the tiles (two per tree node and two per leaf); on an H2_FP64 handle a call
+ * the tiles (two per tree node and two per leaf, 32 wide whatever nrhs is: 1.6 GB
+ * in FP64 for 2^20 points of rank 64); on an H2_FP64 handle a call
  * that finds no memory for them, or comes first while its stream is being
- * captured, runs single-vector products instead.  The first call on an H2_FP32
+ * captured, runs single-vector products instead, and other streams may be
+ * captured meanwhile.  The first call on an H2_FP32
  * or H2_BF16_SCALED handle also times three launch shapes (the block loop's
  * prefetch depth, as listed at h2_batch_tuning: 0, 2 and 6 with 16-wide tiles
  * for passes of at most 16 right-hand sides, else 0, 4 and 5 with 32-wide
@@ -392,8 +394,10 @@ h2_status h2_get_level_bsr(h2_handle A, int level, int64_t *count, int32_t *rowp
 /* Per-phase device times of the products on A, measured with HIP events on
  * the call's stream while enabled (enable != 0 starts recording and clears the
  * totals).  ms: host, 8 doubles: leaf projection + upsweep, coupling and dense
- * streaming, downsweep, leaf expansion and sum, whole call; then calls: host
- * int64 number of calls recorded.  Reading the totals synchronizes the device. */
+ * streaming, downsweep, leaf expansion and sum, whole call (single-vector
+ * products run the levels next to the leaves in the leaf expansion's launch and
+ * count them there); then calls: host int64 number of calls recorded (tile
+ * products: passes of up to 32 right-hand sides).  Reading the totals synchronizes the device. */
 h2_status h2_profile(h2_handle A, int enable);
 h2_status h2_profile_read(h2_handle A, double *ms, int64_t *calls);
 

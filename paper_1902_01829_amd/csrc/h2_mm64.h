@@ -12,8 +12,8 @@
 // the matrix cores (2 x 32 flops per 8 stored bytes at 78.6 TFLOP/s take 0.7
 // of the time the bytes take at 7 TB/s).  2-D, 2^18 points, rank 64: 32
 // right-hand sides 58.1 ms as single-vector products -> 2.8 ms (10.4 GB of
-// blocks; the streaming launch 2.35 ms, 4.4 TB/s), 8 right-hand sides 14.0 ->
-// 2.2 ms.  The block reads alone, without the result tiles' stores, run at
+// blocks; the streaming launch 2.35 ms, 4.4 TB/s, L1 address units 93 % busy,
+// matrix cores 51 %), 8 right-hand sides 14.0 -> 2.2 ms.  The block reads alone, without the result tiles' stores, run at
 // 7.0 TB/s (6.27 ms for the 43.7 GB of the 2^20-point matrix) and the whole
 // launch without its stores takes 6.7 ms (16 right-hand sides) and 7.6 ms
 // (32): the 0.4 and 0.8 GB of tiles written while the HBM is read at its

@@ -230,11 +230,11 @@ void run_tile_pass(h2_matrix_ &A, const double *X, int64_t ldx, double *Y, int64
 }
 
 // Fewest right-hand sides a pass on the FP64 matrix cores is used for.  A pass
-// of up to 16 costs 1.1 to 1.5 single-vector products (2-D, 2^18 points 2.27
-// against 1.79 ms, 60,000 points of rank 49 0.57 against 0.39 ms); stored by
-// halves it reads every block twice, where the single-vector product reads it
-// once, and costs 2.2 to 2.6 of them from 60,000 points up (2.94 against 1.16
-// ms, 0.74 against 0.34 ms).
+// of up to 16 costs 1.2 to 1.85 single-vector products (2-D, 2^18 points 2.23
+// against 1.79 ms, 4,096 points 48 against 31 us; 3-D, 3,000 points of rank 27 60
+// against 33 us); stored by halves it reads every block twice, where the
+// single-vector product reads it once, and costs 2.1 to 2.6 of them from 40,000
+// points up (2-D 2^18 points 2.84 against 1.16 ms), 1.5 and less below.
 int least_columns64(const h2_matrix_ &A) { return A.half ? 3 : 2; }
 
 // Y = A X for an FP64 matrix on the FP64 matrix cores, MM_TILE right-hand
