@@ -51,14 +51,14 @@ inline void check_hip(hipError_t e, const char *where) {
 // one that finds no room drives out those nothing asked for while kStale others
 // came.  None is held while less than 1 / kShare of the device's memory is
 // free, nor once the process has no matrix or batch left, nor after
-// h2_release_kept.  (65,536 points compressed in a loop, which asks for 260 MB
-// in blocks of up to 200 MB beside ones of 1.0 and 2.4 GB: 28.2 ms with 512 MiB,
-// 30.1 with 256 MiB, 28.9 with 1 GiB, where the block of 1.0 GB takes the room.)
+// h2_release_kept.  (Built and compressed in a loop, kLimit 512 MiB / 1 GiB: 3-D,
+// 14,000 points 8.6 / 8.0 ms; 2-D, 38,000 points 18.1 / 16.6, 65,536 29.1 / 29.1;
+// with 256 MiB the last took 30.1 where 512 MiB took 28.2.)
 // A block serves requests of exactly its size, so that what an owner counts is
 // what it holds.  Blocks come here only after a wait for
 // their device, so any stream may use them next.
 struct DevicePool {
-    static constexpr int64_t kLimit = int64_t(512) << 20, kLeast = 64 << 10, kShare = 16;
+    static constexpr int64_t kLimit = int64_t(1) << 30, kLeast = 64 << 10, kShare = 16;
     static constexpr int64_t kStale = 256;
     struct Block {
         int device;

@@ -6,7 +6,7 @@ using h2i::DeviceArena;
 
 int main(int, char **argv) {
     const std::string what = argv[1];
-    constexpr int64_t MiB = 1 << 20, bound = 512 * MiB;
+    constexpr int64_t MiB = 1 << 20, bound = 1024 * MiB;
     h2_matrix_ *A = fake::matrix(2, H2_FP64), *B = fake::matrix(2, H2_FP64);
     auto dropped = [](int blocks, int64_t bytes) {   // an owner of so many blocks that comes and goes
         DeviceArena a;
@@ -14,7 +14,7 @@ int main(int, char **argv) {
         for (int k = 0; k < blocks; ++k) a.alloc(bytes);
     };
     if (what == "bound") {
-        for (int k = 0; k < 5; ++k) dropped(12, 48 * MiB);
+        for (int k = 0; k < 5; ++k) dropped(12, 96 * MiB);
         CHECK(fake::used <= bound);
         dropped(2, 2 * bound);
         CHECK(fake::used <= bound);
@@ -24,11 +24,11 @@ int main(int, char **argv) {
             dropped(blocks, bytes);
             return fake::mallocs - before;
         };
-        for (int k = 0; k < 100; ++k) dropped(8, 16 * MiB);
-        CHECK(mallocs_of(8, 16 * MiB) == 1 && fake::used <= bound);
+        for (int k = 0; k < 100; ++k) dropped(8, 32 * MiB);
+        CHECK(mallocs_of(8, 32 * MiB) == 1 && fake::used <= bound);
         // more than there is room for, in turn: as much as fits is found each time
-        for (int k = 0; k < 100; ++k) dropped(40, 16 * MiB);
-        CHECK(mallocs_of(40, 16 * MiB) == 1 + 8 && fake::used <= bound);
+        for (int k = 0; k < 100; ++k) dropped(40, 32 * MiB);
+        CHECK(mallocs_of(40, 32 * MiB) == 1 + 8 && fake::used <= bound);
     } else if (what == "given_back") {
         dropped(4, 16 * MiB);
         CHECK(fake::used > 0);

@@ -58,6 +58,6 @@ def test_kept_memory_serves_its_own_size(kept):
 
 @pytest.mark.parametrize("what", ["bound", "given_back", "release", "short_memory"])
 def test_memory_kept_for_later_calls(kept, what):
-    """At most 512 MiB, of sizes that are asked for; all given back with the last
+    """At most 1 GiB, of sizes that are asked for; all given back with the last
     handle, on request, and where the device is short of memory."""
     _check(kept, what)
