@@ -370,7 +370,8 @@ void h2_free(h2_handle A);
 /* Give the device memory kept for later calls back to the device.  Of what
  * h2_free, h2_batch_free and the scratch of set-up calls give up, the process
  * keeps at most 1 GiB, and only while it has a matrix or a batch and more
- * than a sixteenth of the device's memory is free; none of it belongs to a
+ * than a sixteenth of the device's memory is free (looked up whenever what is kept
+ * grows, and at every 64th release); none of it belongs to a
  * handle or is counted in bytes_device_total, and a device allocation of this
  * library that fails returns it and tries again.  May be called from any
  * thread, like h2_free not while a stream is being captured; waits for the

@@ -49,9 +49,15 @@ int main(int, char **argv) {
         dropped(4, 16 * MiB);
         DeviceArena other;
         fake::budget = 1600 * MiB;
-        other.alloc(1480 * MiB);
+        other.alloc(1510 * MiB);
         dropped(1, 2 * MiB);
         CHECK(fake::used == other.bytes);
+        fake::budget = int64_t(1) << 40;
+        h2_release_kept();
+        dropped(1, 2 * MiB);
+        const int queries = fake::queries;
+        for (int k = 0; k < 128; ++k) dropped(1, 2 * MiB);   // a loop looks up now and then
+        CHECK(fake::queries - queries <= 2 && fake::used == other.bytes + 2 * MiB);
     } else if (what == "sizes") {
         // an owner holds no more than it counts
         dropped(2, 20 * MiB);
